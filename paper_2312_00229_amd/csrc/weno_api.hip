@@ -39,38 +39,42 @@ __device__ __forceinline__ StripCtx make_ctx(const FwdJob& jb, int n, int c, flo
     cx.src_shift = jb.src_shift;
     cx.src_h = jb.src_h;
     cx.src_w = jb.src_w;
-    cx.in_u8 = jb.in_u8;
-    cx.out_u8 = jb.out_u8;
-    cx.vec = jb.vec;
     cx.out_scale = out_scale;
     return cx;
 }
 
 // TAIL (two columns only): the launch has one-column tail strips
 // (jb.tail_rows > 0) and one wave index across the planes
+// Two-column kernels are held to 168 VGPRs, three waves per SIMD: strided float
+// destinations would take 170 (two to four values spill).
 template <int COLS, int BETA, int IO, bool PACED, bool TAIL = false>
-__global__ __launch_bounds__(kBlock) void zoom2x_kernel(FwdJob jb, FwdParams P, int rows_per_strip)
+__global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJob jb, FwdParams P, int rows_per_strip)
 {
     // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.
     // Renumber them so that every XCD gets a contiguous range of strips
     // (whole bands of adjacent rows): the 9 halo rows a strip shares with the
     // strip above are then re-read from the same L2.  A bijection on
     // [0, gridDim.x).  The XCD of a workgroup is its linear index (plane-major)
-    // mod 8.  For images whose planes are interleaved (HWC) the host pads
-    // gridDim.x to a multiple of 8: the same strip of every plane then runs
-    // on the same XCD, and the lines the planes share meet in one L2 instead
-    // of reaching HBM once per plane with a third of their bytes each (1080p
-    // RGB uint8: writes 3.0x -> 1.0x the output, reads 4.1x -> 1.1x the
-    // input).  Otherwise the XCD of a strip rotates from plane to plane,
-    // which spreads the planes' workgroups evenly over the XCDs.  With tail
-    // strips the grid is one-dimensional and every XCD gets a contiguous
-    // range of waves, plane after plane.
+    // mod 8, so the XCD of a strip rotates from plane to plane, which spreads
+    // the planes' workgroups evenly over the XCDs.  With tail strips the grid
+    // is one-dimensional and every XCD gets a contiguous range of waves, plane
+    // after plane.  For images whose planes are interleaved (HWC) the grid is
+    // one-dimensional too, a multiple of 8 workgroups per plane, and on each
+    // XCD a strip's workgroups of all the planes follow each other: the lines
+    // the planes share meet in one L2 while they are there, instead of reaching
+    // HBM once per plane with a third of their bytes each (1080p RGB uint8:
+    // writes 3.0x -> 1.0x the output, reads 4.1x -> 1.1x the input).
     const int nb = gridDim.x, b = blockIdx.x;
     const int xcd = b % kXcds, k = b / kXcds;
     const int logical = xcd * (nb / kXcds) + min(xcd, nb % kXcds) + k;
     // the wave index is the same in every lane; say so, so that strip rows and
     // buffer offsets live in SGPRs
     const int wave = __builtin_amdgcn_readfirstlane(logical * kWavesPerBlock + (threadIdx.x >> 6));
+    float* stage = nullptr;
+    if constexpr (stage_floats<COLS, IO>() > 0) {
+        __shared__ float rows[kWavesPerBlock * stage_floats<COLS, IO>()];
+        stage = rows + (threadIdx.x >> 6) * stage_floats<COLS, IO>();
+    }
     if constexpr (TAIL) {
         // One wave index across the planes (gridDim.y is 1).  Per plane: the
         // two-column strips, band by band, then the one-column strips of the
@@ -86,22 +90,33 @@ __global__ __launch_bounds__(kBlock) void zoom2x_kernel(FwdJob jb, FwdParams P, 
         if (w < n2) {
             const int sy = w / jb.strips_x, sx = w - sy * jb.strips_x;
             const int R0 = sy * rows_per_strip;
-            zoom_strip<2, BETA, IO, PACED>(cx, P, sx * strip_own<2>(), R0, min(R0 + rows_per_strip, jb.H));
+            zoom_strip<2, BETA, IO, PACED>(cx, P, sx * strip_own<2>(), R0, min(R0 + rows_per_strip, jb.H),
+                                           stage);
         } else {
             const int R0 = (w - n2) * jb.tail_rows;
-            zoom_strip<1, BETA, IO, PACED>(cx, P, jb.strips_x * strip_own<2>(), R0, min(R0 + jb.tail_rows, jb.H));
+            zoom_strip<1, BETA, IO, PACED>(cx, P, jb.strips_x * strip_own<2>(), R0, min(R0 + jb.tail_rows, jb.H),
+                                           stage);
         }
     } else {
-        const int per_plane = jb.strips_x * jb.strips_y;
-        if (wave >= per_plane) return;  // whole wave
-        const int plane = blockIdx.y;
-        const int sy = wave / jb.strips_x;
-        const int sx = wave - sy * jb.strips_x;
-        const int n = plane / jb.C, c = plane - n * jb.C;
+        int n, c, w = wave;
+        if (jb.share) {
+            // on each XCD: image by image, workgroup by workgroup, plane by plane
+            const int per_xcd = nb / (kXcds * jb.planes);
+            n = k / (per_xcd * jb.C);
+            const int r = k - n * per_xcd * jb.C;
+            c = r % jb.C;
+            w = __builtin_amdgcn_readfirstlane((xcd * per_xcd + r / jb.C) * kWavesPerBlock + (threadIdx.x >> 6));
+        } else {
+            n = blockIdx.y / jb.C;
+            c = blockIdx.y - n * jb.C;
+        }
+        if (w >= jb.strips_x * jb.strips_y) return;  // whole wave
+        const int sy = w / jb.strips_x;
+        const int sx = w - sy * jb.strips_x;
         const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
         const int R0 = sy * rows_per_strip;
         const int R1 = min(R0 + rows_per_strip, jb.H);
-        zoom_strip<COLS, BETA, IO, PACED>(cx, P, sx * strip_own<COLS>(), R0, R1);
+        zoom_strip<COLS, BETA, IO, PACED>(cx, P, sx * strip_own<COLS>(), R0, R1, stage);
     }
 }
 
@@ -120,6 +135,8 @@ __global__ __launch_bounds__(kBlock) void zoom2x_batched_kernel(const BatchTable
     const int64_t total = tab->total_items;
     const FwdJob* __restrict__ jobs = batch_jobs(tab);
     const int64_t* __restrict__ prefix = batch_prefix(tab);
+    __shared__ float rows[kWavesPerBlock * stage_floats<COLS, kIoF32S>()];
+    float* const stage = rows + (threadIdx.x >> 6) * stage_floats<COLS, kIoF32S>();
     for (;;) {
         unsigned long long got = 0;
         if (lane == 0) got = atomicAdd(counter, 1ull);
@@ -153,7 +170,8 @@ __global__ __launch_bounds__(kBlock) void zoom2x_batched_kernel(const BatchTable
         case kIoU8: zoom_strip<COLS, BETA, kIoU8>(cx, P, sx * strip_own<COLS>(), R0, R1); break;
         case kIoU8F32: zoom_strip<COLS, BETA, kIoU8F32>(cx, P, sx * strip_own<COLS>(), R0, R1); break;
         case kIoF32U8: zoom_strip<COLS, BETA, kIoF32U8>(cx, P, sx * strip_own<COLS>(), R0, R1); break;
-        default: zoom_strip<COLS, BETA, kIoGeneric>(cx, P, sx * strip_own<COLS>(), R0, R1); break;
+        case kIoF32S: zoom_strip<COLS, BETA, kIoF32S>(cx, P, sx * strip_own<COLS>(), R0, R1, stage); break;
+        default: zoom_strip<COLS, BETA, kIoU8F32S>(cx, P, sx * strip_own<COLS>(), R0, R1, stage); break;
         }
     }
 }
@@ -310,6 +328,13 @@ int wz_beta_mode(float beta)
     return kBetaGeneral;
 }
 
+// Planes of one image interleaved in memory (channels closer together than
+// rows, as in HWC): the same strip of its planes touches the same lines.
+static bool planes_share_lines(int C, int64_t sc, int64_t sh)
+{
+    return C > 1 && std::llabs(sc) < std::llabs(sh);
+}
+
 // Fill a FwdJob for src -> dst (shapes already validated).
 // The readable source region of src for a boundary mode: src itself, or
 // (WENO_BOUNDARY_EXTERNAL) rows -4 .. h+4 and columns -4 .. w+4 around it.
@@ -359,22 +384,13 @@ FwdJob wz_make_job(const weno_tensor_t* src, const weno_tensor_t* dst, int cols,
         jb.tail_rows = tail_rows;
         jb.tail_bands = (src->h + tail_rows - 1) / tail_rows;
     }
-    // vector stores need contiguous rows and aligned plane/row starts
-    const uintptr_t base = (uintptr_t)dst->data;
-    int vec = 0;
-    if (!jb.out_u8 && dst->sw == 1) {
-        const bool a8 = base % 8 == 0 && (jb.d_h % 8 == 0) && (jb.d_n % 8 == 0) && (jb.d_c % 8 == 0);
-        const bool a16 = base % 16 == 0 && (jb.d_h % 16 == 0) && (jb.d_n % 16 == 0) && (jb.d_c % 16 == 0);
-        vec = a16 ? 2 : (a8 ? 1 : 0);
-    }
-    jb.vec = vec;
-    // fixed-layout I/O modes where the layout allows (float rows need vector
-    // stores: contiguous, aligned destination columns)
-    const bool vec_rows = cols == 2 ? vec == 2 : vec >= 1;
-    if (jb.in_u8 && jb.out_u8) jb.io = kIoU8;
-    else if (!jb.in_u8 && jb.out_u8) jb.io = kIoF32U8;
-    else if (!vec_rows) jb.io = kIoGeneric;
-    else jb.io = jb.in_u8 ? kIoU8F32 : kIoF32;
+    jb.share = planes_share_lines(jb.C, jb.s_c, jb.s_h) || planes_share_lines(jb.C, jb.d_c, jb.d_h);
+    // vector stores need contiguous columns and 4-byte aligned elements (what
+    // a float tensor has)
+    const bool vec_rows = dst->sw == 1 && (uintptr_t)dst->data % 4 == 0;
+    if (jb.out_u8) jb.io = jb.in_u8 ? kIoU8 : kIoF32U8;
+    else if (vec_rows) jb.io = jb.in_u8 ? kIoU8F32 : kIoF32;
+    else jb.io = jb.in_u8 ? kIoU8F32S : kIoF32S;
     jb.dst_extent = (uint32_t)wz_plane_extent(dst);
     weno_tensor_t region;
     wz_source_region(src, boundary, &region);   // validated by the caller
@@ -435,16 +451,9 @@ static int fwd_resident_blocks()
     return v;
 }
 
-// Planes of one image interleaved in memory (channels closer together than
-// rows, as in HWC): the same strip of its planes touches the same lines.
-static bool planes_share_lines(int C, int64_t sc, int64_t sh)
-{
-    return C > 1 && std::llabs(sc) < std::llabs(sh);
-}
-
-// Workgroups along x for a plane of `strips` strips: padded to a multiple of
-// the XCD count when the planes share lines (zoom2x_kernel), the padding
-// exiting at once.  The busiest XCD then holds planes x grid_x / 8 of them.
+// Workgroups of a plane of `strips` strips: padded to a multiple of the XCD
+// count when the planes share lines (zoom2x_kernel), the padding exiting at
+// once.  The busiest XCD then holds planes x grid_x / 8 of them.
 static int fwd_grid_x(int64_t strips, bool share)
 {
     const int64_t bx = (strips + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -456,8 +465,8 @@ static int fwd_grid_x(int64_t strips, bool share)
 template <int COLS, int BETA, int IO>
 static hipError_t launch_fwd_beta(const FwdJob& jb, const FwdParams& P, int rows, hipStream_t st)
 {
-    const bool share = planes_share_lines(jb.C, jb.s_c, jb.s_h) || planes_share_lines(jb.C, jb.d_c, jb.d_h);
-    dim3 grid(fwd_grid_x((int64_t)jb.strips_x * jb.strips_y, share), jb.planes);
+    dim3 grid(fwd_grid_x((int64_t)jb.strips_x * jb.strips_y, jb.share), jb.planes);
+    if (jb.share) grid = dim3(grid.x * grid.y, 1);   // the planes' workgroups interleaved (zoom2x_kernel)
     if constexpr (COLS == 2) {
         if (jb.tail_rows > 0) {  // one wave index across the planes
             const int64_t waves = (int64_t)jb.planes * ((int64_t)jb.strips_x * jb.strips_y + jb.tail_bands);
@@ -494,7 +503,8 @@ static hipError_t launch_fwd_cols(const FwdJob& jb, const FwdParams& P, int beta
     case kIoU8: return launch_fwd_io<COLS, kIoU8>(jb, P, beta_mode, rows, st);
     case kIoU8F32: return launch_fwd_io<COLS, kIoU8F32>(jb, P, beta_mode, rows, st);
     case kIoF32U8: return launch_fwd_io<COLS, kIoF32U8>(jb, P, beta_mode, rows, st);
-    default: return launch_fwd_io<COLS, kIoGeneric>(jb, P, beta_mode, rows, st);
+    case kIoF32S: return launch_fwd_io<COLS, kIoF32S>(jb, P, beta_mode, rows, st);
+    default: return launch_fwd_io<COLS, kIoU8F32S>(jb, P, beta_mode, rows, st);
     }
 }
 

@@ -50,18 +50,29 @@ constexpr int kXcds = 8;  // MI355X: accelerator complex dies, one L2 each
 // beta specialisations
 constexpr int kBetaGeneral = -1;
 
-// I/O modes of the strip walk.  The two common layouts are fixed at compile
-// time so that every row issues the same memory operations, with no branch:
-// the compiler can then keep prefetched rows in flight across iterations.
-constexpr int kIoGeneric = 0;  // any dtype pair, strides and output scale (runtime flags)
-constexpr int kIoF32 = 1;      // f32 -> f32, destination columns contiguous and vector-aligned
-constexpr int kIoU8 = 2;       // u8 -> u8, any strides
-constexpr int kIoU8F32 = 3;    // u8 -> f32 (x 1/255), destination as for kIoF32
-constexpr int kIoF32U8 = 4;    // f32 -> u8 (x 255), any strides
-constexpr bool io_in_u8(int io) { return io == kIoU8 || io == kIoU8F32; }
+// I/O modes of the strip walk, fixed at compile time so that every row issues
+// the same memory operations, with no branch: the compiler can then keep
+// prefetched rows in flight across iterations.  Every pair of types and every
+// stride has one: float rows with contiguous columns are stored a vector per
+// lane, all other destinations element by element.  (A runtime-flag path
+// served the strided and the odd-width float rows before: branches around
+// each row's stores and two rows per trip: 3x1440x2560 uint8 HWC to float32
+// HWC 194 -> 78 us without it, 3x719x1277 float32 23.5 -> 19.0 us.)
+constexpr int kIoF32 = 0;      // f32 -> f32, destination columns contiguous
+constexpr int kIoU8 = 1;       // u8 -> u8, any strides
+constexpr int kIoU8F32 = 2;    // u8 -> f32 (x 1/255), destination as for kIoF32
+constexpr int kIoF32U8 = 3;    // f32 -> u8 (x 255), any strides
+constexpr int kIoF32S = 4;     // f32 -> f32, any strides
+constexpr int kIoU8F32S = 5;   // u8 -> f32, any strides
+constexpr bool io_in_u8(int io) { return io == kIoU8 || io == kIoU8F32 || io == kIoU8F32S; }
 constexpr bool io_out_u8(int io) { return io == kIoU8 || io == kIoF32U8; }
+// float rows stored a vector per lane
+constexpr bool io_out_vec(int io) { return io == kIoF32 || io == kIoU8F32; }
+// float rows with spread columns (HWC) are stored element by element, in column
+// order across the wave (store_quads)
+constexpr bool io_out_staged(int io) { return io == kIoF32S || io == kIoU8F32S; }
 // the output scale is 1 when both ends have the same dtype
-constexpr bool io_scaled(int io) { return io == kIoU8F32 || io == kIoF32U8; }
+constexpr bool io_scaled(int io) { return io_in_u8(io) != io_out_u8(io); }
 
 // A buffer offset past every plane extent (planes span less than 2^31 bytes):
 // loads through it return 0 and stores through it are dropped by the buffer
@@ -84,13 +95,13 @@ struct FwdJob {
     int32_t H, W, C, planes;          // planes = N * C
     int64_t s_n, s_c, s_h, s_w;       // byte strides of the source
     int64_t d_n, d_c, d_h, d_w;       // byte strides of the destination
-    int32_t in_u8, out_u8;            // element types
+    int32_t in_u8, out_u8;            // element types (host)
     int32_t strips_x, strips_y;       // strips per plane (two-column strips only when tail_rows > 0)
     // tail_rows > 0: the columns left of the last two-column strip are
     // walked by one-column strips of tail_rows rows, tail_bands of them per
     // plane (single-image planar launches; zoom2x_kernel)
     int32_t tail_rows, tail_bands;
-    int32_t vec;                      // 2: float4 rows, 1: float2 rows, 0: scalar stores
+    int32_t share;                    // planes interleaved in memory: their strips' workgroups run together
     uint32_t src_extent, dst_extent;  // bytes spanned by one plane (< 2^31)
     int32_t io;                       // I/O mode (kIo*)
     // readable source region: src points at its element (0, 0), which is
@@ -183,13 +194,14 @@ struct StripState {
 template <int COLS>
 struct StripLanes {
     uint32_t src_off[COLS];  // source column byte offsets (columns clamped to the image)
-    int J[COLS];             // input column of each of the lane's columns
-    bool own[COLS];          // column stored by this strip
-    bool own_all;
-    uint32_t st_col[COLS];   // kIoU8: destination column offsets, kOob where not owned
-    uint32_t st_vec;         // kIoF32: offset of the lane's vector store, kOob unless all its columns are owned
-    uint32_t st_half;        // kIoF32, two columns: offset of a 2-float store when only column 0 is owned, else kOob
+    uint32_t st_col[COLS];   // byte stores: destination column offsets, kOob where not owned
+    uint32_t st_out[2 * COLS];   // staged stores: offsets of the strip's owned output columns 64 i + lane, else kOob
+    float* stage_wr;         // staged stores: this lane's 2*COLS outputs in the wave's LDS rows
+    const float* stage_rd;   // staged stores: the strip's owned output column `lane` in them
+    uint32_t st_vec;         // vector stores: offset of the lane's store, kOob unless all its columns are owned
+    uint32_t st_half;        // vector stores, two columns: offset of a 2-float store when only column 0 is owned, else kOob
     bool any_half;           // some lane of the strip needs st_half (odd width, last strip); uniform
+    bool split;              // true, unknown to the compiler: ends a basic block at every row's stores
 };
 
 // Buffer resources (gfx9 family descriptor, raw addressing): the plane base
@@ -254,7 +266,6 @@ struct StripCtx {
     uint32_t s_w_bytes;       // source column stride
     int32_t H, W;
     int32_t src_shift, src_h, src_w;   // readable source region (FwdJob)
-    int32_t in_u8, out_u8, vec;
     float out_scale;
 };
 
@@ -272,8 +283,7 @@ __device__ __forceinline__ void load_row_raw(const StripCtx& cx, const uint32_t 
     const int rs = r + cx.src_shift;
     const int rc = rs < 0 ? 0 : (rs >= cx.src_h ? cx.src_h - 1 : rs);
     const uint32_t soff = (uint32_t)rc * cx.s_h;
-    const bool u8 = io_in_u8(IO) || (IO == kIoGeneric && cx.in_u8);
-    if (u8) {
+    if constexpr (io_in_u8(IO)) {
 #pragma unroll
         for (int c = 0; c < COLS; ++c) q[c] = __builtin_amdgcn_raw_buffer_load_b8(cx.src, (int)off[c], (int)soff, 0);
     } else {
@@ -283,10 +293,11 @@ __device__ __forceinline__ void load_row_raw(const StripCtx& cx, const uint32_t 
 }
 
 template <int IO>
-__device__ __forceinline__ float raw_value(const StripCtx& cx, raw_t<IO> q)
+__device__ __forceinline__ float raw_value(raw_t<IO> q)
 {
-    if constexpr (io_in_u8(IO)) return (float)q;
-    else if constexpr (IO != kIoGeneric) {
+    if constexpr (io_in_u8(IO)) {
+        return (float)q;
+    } else {
         // an explicit copy into a register of its own: the slot's register is
         // then free for the row loaded next, so it stays the loop-carried
         // register and is not copied (waiting for that load) at the back edge
@@ -294,7 +305,6 @@ __device__ __forceinline__ float raw_value(const StripCtx& cx, raw_t<IO> q)
         asm("v_mov_b32 %0, %1" : "=&v"(v) : "v"(q));
         return v;
     }
-    else return cx.in_u8 ? (float)q : __builtin_bit_cast(float, q);
 }
 
 // clamp(round-half-even(u), 0, 255), NaN -> 0, in one instruction:
@@ -304,13 +314,15 @@ __device__ __forceinline__ float raw_value(const StripCtx& cx, raw_t<IO> q)
 // and NaN)
 __device__ __forceinline__ uint32_t quant_u8(float u) { return __builtin_amdgcn_cvt_pk_u8_f32(u, 0u, 0u); }
 
-// store the 2x2 quads of row R for this lane's columns: fixed layouts,
-// branch-free (lanes that own nothing store through kOob).  Mixed dtypes
-// scale by out_scale (255 or 1/255), as the runtime-flag path does.
+// store the 2x2 quads of row R for this lane's columns, branch-free (lanes
+// that own nothing store through kOob).  Mixed dtypes scale by out_scale (255
+// or 1/255).  A vector store needs only 4-byte alignment, so float rows of
+// any pitch take it: 3x719x1277, whose rows are 8-byte aligned, is stored
+// through dwordx4 as 3x720x1280 is.
 template <int COLS, int IO, int ST>
-__device__ __forceinline__ void store_quads_fixed(const StripCtx& cx, int R, const StripLanes<COLS>& L,
-                                                  const float (&o00)[COLS], const float (&o01)[COLS],
-                                                  const float (&o10)[COLS], const float (&o11)[COLS])
+__device__ __forceinline__ void store_quads(const StripCtx& cx, int R, const StripLanes<COLS>& L,
+                                            const float (&o00)[COLS], const float (&o01)[COLS],
+                                            const float (&o10)[COLS], const float (&o11)[COLS])
 {
     const uint32_t r0 = (uint32_t)(2 * R) * cx.d_h;
     const uint32_t r1 = r0 + cx.d_h;
@@ -324,7 +336,7 @@ __device__ __forceinline__ void store_quads_fixed(const StripCtx& cx, int R, con
             a[k] = o00[k]; b[k] = o01[k]; c[k] = o10[k]; d[k] = o11[k];
         }
     }
-    if constexpr (!io_out_u8(IO)) {
+    if constexpr (io_out_vec(IO)) {
         if constexpr (COLS == 2) {
             buf_st_f32x4<ST>(a[0], b[0], a[1], b[1], cx.dst, L.st_vec, r0);
             buf_st_f32x4<ST>(c[0], d[0], c[1], d[1], cx.dst, L.st_vec, r1);
@@ -336,67 +348,37 @@ __device__ __forceinline__ void store_quads_fixed(const StripCtx& cx, int R, con
             buf_st_f32x2<ST>(a[0], b[0], cx.dst, L.st_vec, r0);
             buf_st_f32x2<ST>(c[0], d[0], cx.dst, L.st_vec, r1);
         }
-    } else {  // one byte per output
+    } else if constexpr (io_out_staged(IO)) {
+        // A lane's 2*COLS outputs of a row pass through the wave's LDS rows,
+        // so that a store takes 64 neighbouring output columns.  Stored from
+        // where they are, a lane's outputs lie 2*COLS columns apart from the
+        // next lane's (48 bytes in HWC RGB): every lane of every store is then
+        // an L2 request of its own, 512 per row of quads, and those bind the
+        // launch (3x1440x2560 uint8 HWC to float32 HWC: 165 us); in column
+        // order five lanes share one (78 us).  LDS serves a wave's accesses in
+        // order, so no barrier is needed.
+        constexpr int N = 2 * COLS, PITCH = kWave * N;
 #pragma unroll
         for (int k = 0; k < COLS; ++k) {
-            const uint32_t off0 = L.st_col[k];
-            buf_st_u8(quant_u8(a[k]), cx.dst, off0, r0);
-            buf_st_u8(quant_u8(b[k]), cx.dst, off0 + cx.d_w, r0);
-            buf_st_u8(quant_u8(c[k]), cx.dst, off0, r1);
-            buf_st_u8(quant_u8(d[k]), cx.dst, off0 + cx.d_w, r1);
+            L.stage_wr[2 * k] = a[k];
+            L.stage_wr[2 * k + 1] = b[k];
+            L.stage_wr[PITCH + 2 * k] = c[k];
+            L.stage_wr[PITCH + 2 * k + 1] = d[k];
         }
-    }
-}
-
-// store the 2x2 quads of row R for this lane's columns (any layout)
-template <int COLS, int ST>
-__device__ __forceinline__ void store_quads(const StripCtx& cx, int R, const int (&J)[COLS], bool own_all,
-                                            const bool (&own)[COLS], const float (&o00)[COLS],
-                                            const float (&o01)[COLS], const float (&o10)[COLS],
-                                            const float (&o11)[COLS])
-{
-    const uint32_t r0 = (uint32_t)(2 * R) * cx.d_h;
-    const uint32_t r1 = r0 + cx.d_h;
-    if (!cx.out_u8 && cx.out_scale == 1.0f && COLS == 2 && cx.vec == 2 && own_all) {
-        // same dtype in and out: no rescaling
-        const uint32_t off = (uint32_t)(2 * J[0]) * 4u;
-        buf_st_f32x4<ST>(o00[0], o01[0], o00[COLS - 1], o01[COLS - 1], cx.dst, off, r0);
-        buf_st_f32x4<ST>(o10[0], o11[0], o10[COLS - 1], o11[COLS - 1], cx.dst, off, r1);
-    } else if (!cx.out_u8) {
-        const float s = cx.out_scale;
-        if (COLS == 2 && cx.vec == 2 && own_all) {
-            const uint32_t off = (uint32_t)(2 * J[0]) * 4u;
-            buf_st_f32x4<ST>(o00[0] * s, o01[0] * s, o00[COLS - 1] * s, o01[COLS - 1] * s, cx.dst, off, r0);
-            buf_st_f32x4<ST>(o10[0] * s, o11[0] * s, o10[COLS - 1] * s, o11[COLS - 1] * s, cx.dst, off, r1);
-        } else if (cx.vec >= 1) {
+        if (L.split) {
 #pragma unroll
-            for (int c = 0; c < COLS; ++c) {
-                if (!own[c]) continue;
-                const uint32_t off = (uint32_t)(2 * J[c]) * 4u;
-                buf_st_f32x2(o00[c] * s, o01[c] * s, cx.dst, off, r0);
-                buf_st_f32x2(o10[c] * s, o11[c] * s, cx.dst, off, r1);
-            }
-        } else {
-#pragma unroll
-            for (int c = 0; c < COLS; ++c) {
-                if (!own[c]) continue;
-                const uint32_t off0 = (uint32_t)(2 * J[c]) * cx.d_w;
-                buf_st_f32(o00[c] * s, cx.dst, off0, r0);
-                buf_st_f32(o01[c] * s, cx.dst, off0 + cx.d_w, r0);
-                buf_st_f32(o10[c] * s, cx.dst, off0, r1);
-                buf_st_f32(o11[c] * s, cx.dst, off0 + cx.d_w, r1);
+            for (int i = 0; i < N; ++i) {
+                buf_st_f32(L.stage_rd[kWave * i], cx.dst, L.st_out[i], r0);
+                buf_st_f32(L.stage_rd[PITCH + kWave * i], cx.dst, L.st_out[i], r1);
             }
         }
-    } else {
-        const float s = cx.out_scale;
+    } else {  // one byte per store; the odd columns through the scalar row offset
 #pragma unroll
-        for (int c = 0; c < COLS; ++c) {
-            if (!own[c]) continue;
-            const uint32_t off0 = (uint32_t)(2 * J[c]) * cx.d_w;
-            buf_st_u8(quant_u8(o00[c] * s), cx.dst, off0, r0);
-            buf_st_u8(quant_u8(o01[c] * s), cx.dst, off0 + cx.d_w, r0);
-            buf_st_u8(quant_u8(o10[c] * s), cx.dst, off0, r1);
-            buf_st_u8(quant_u8(o11[c] * s), cx.dst, off0 + cx.d_w, r1);
+        for (int k = 0; k < COLS; ++k) {
+            buf_st_u8(quant_u8(a[k]), cx.dst, L.st_col[k], r0);
+            buf_st_u8(quant_u8(b[k]), cx.dst, L.st_col[k], r0 + cx.d_w);
+            buf_st_u8(quant_u8(c[k]), cx.dst, L.st_col[k], r1);
+            buf_st_u8(quant_u8(d[k]), cx.dst, L.st_col[k], r1 + cx.d_w);
         }
     }
 }
@@ -421,7 +403,7 @@ __device__ __forceinline__ void strip_step(StripState<COLS>& s, raw_t<IO> (&Q)[C
     float V5[COLS], H5[COLS], S5[COLS];
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
-        V5[c] = raw_value<IO>(cx, Q[c]);
+        V5[c] = raw_value<IO>(Q[c]);
         H5[c] = half_of(V5[c]);
         S5[c] = kappa_of(V5[c]);
     }
@@ -553,9 +535,7 @@ __device__ __forceinline__ void strip_step(StripState<COLS>& s, raw_t<IO> (&Q)[C
             Bq[c] = blend4<BETA>(tb[0], tb[1], tb[2], tb[3], s.PB0[0][c], s.PB0[1][c], s.PB0[2][c],
                                  s.PB0[3][c], P.beta);
         }
-        if constexpr (IO == kIoGeneric) {
-            store_quads<COLS, ST>(cx, R, L.J, L.own_all, L.own, s.V0, Bq, Aq, s.X0);
-        } else if constexpr (io_out_u8(IO)) {
+        if constexpr (io_out_u8(IO)) {
             // byte outputs are rounded anyway: the originals and x values are
             // rebuilt from their halves (exact for every normal float), so the
             // raw windows are dead and the kernel keeps three waves per SIMD
@@ -565,9 +545,9 @@ __device__ __forceinline__ void strip_step(StripState<COLS>& s, raw_t<IO> (&Q)[C
                 v0[c] = s.H0[c] + s.H0[c];
                 x0[c] = s.XH0[c] + s.XH0[c];
             }
-            store_quads_fixed<COLS, IO, ST>(cx, R, L, v0, Bq, Aq, x0);
+            store_quads<COLS, IO, ST>(cx, R, L, v0, Bq, Aq, x0);
         } else {
-            store_quads_fixed<COLS, IO, ST>(cx, R, L, s.V0, Bq, Aq, s.X0);
+            store_quads<COLS, IO, ST>(cx, R, L, s.V0, Bq, Aq, s.X0);
         }
     }
 
@@ -600,34 +580,58 @@ constexpr int strip_own() { return COLS == 1 ? kWave - 9 : 2 * kWave - 10; }
 // Walk one strip: owned columns [c0, c0 + strip_own), output rows [R0, R1).
 // PACED: the launch runs as one round of waves (every wave resident from the
 // start): pace the waves that share a SIMD and write whole output rows
-// through the L2.
+// through the L2.  stage: the wave's stage_floats<COLS, IO>() floats of LDS
+// (two rows of 2*COLS outputs per lane; lanes that store nothing read up to 8
+// floats past them).
+template <int COLS, int IO>
+constexpr int stage_floats() { return io_out_staged(IO) ? 2 * kWave * 2 * COLS + 16 : 0; }
+
 template <int COLS, int BETA, int IO, bool PACED = false>
-__device__ __forceinline__ void zoom_strip(const StripCtx& cx, const FwdParams& P, int c0, int R0, int R1)
+__device__ __forceinline__ void zoom_strip(const StripCtx& cx, const FwdParams& P, int c0, int R0, int R1,
+                                           float* stage = nullptr)
 {
-    constexpr int ST = PACED ? kStRows : 0;
+    constexpr int ST = PACED && io_out_vec(IO) ? kStRows : 0;
     constexpr int HALO_L = 4;
     constexpr int OWN = strip_own<COLS>();
     const int lane = threadIdx.x & (kWave - 1);
     const int Jbase = c0 - HALO_L;
     StripLanes<COLS> L;
-    L.own_all = true;
+    int J[COLS];
+    bool own[COLS], own_all = true;
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
         const int sidx_ = lane * COLS + c;
-        L.J[c] = Jbase + sidx_;
-        L.own[c] = (sidx_ >= HALO_L) && (sidx_ < HALO_L + OWN) && (L.J[c] < cx.W);
-        L.own_all = L.own_all && L.own[c];
-        const int js = L.J[c] + cx.src_shift;
+        J[c] = Jbase + sidx_;
+        own[c] = (sidx_ >= HALO_L) && (sidx_ < HALO_L + OWN) && (J[c] < cx.W);
+        own_all = own_all && own[c];
+        const int js = J[c] + cx.src_shift;
         const int jc = js < 0 ? 0 : (js >= cx.src_w ? cx.src_w - 1 : js);
         L.src_off[c] = (uint32_t)jc * cx.s_w_bytes;
-        L.st_col[c] = L.own[c] ? (uint32_t)(2 * L.J[c]) * cx.d_w : kOob;
+        L.st_col[c] = own[c] ? (uint32_t)(2 * J[c]) * cx.d_w : kOob;
     }
     // f32 rows: the lane's 2*COLS floats of an output row are contiguous
-    L.st_vec = L.own_all ? (uint32_t)(2 * L.J[0]) * 4u : kOob;
+    L.st_vec = own_all ? (uint32_t)(2 * J[0]) * 4u : kOob;
     // odd width: the lane holding column W-1 also holds W, past the image
-    const bool half = COLS == 2 && L.own[0] && !L.own_all;
-    L.st_half = half ? (uint32_t)(2 * L.J[0]) * 4u : kOob;
+    const bool half = COLS == 2 && own[0] && !own_all;
+    L.st_half = half ? (uint32_t)(2 * J[0]) * 4u : kOob;
     L.any_half = COLS == 2 && (cx.W & 1) && cx.W - 1 >= Jbase + HALO_L && cx.W - 1 < Jbase + HALO_L + OWN;
+    if constexpr (io_out_staged(IO)) {
+        const int outs = 2 * min(OWN, cx.W - c0);   // the strip's owned output columns, from 2 c0 on
+#pragma unroll
+        for (int i = 0; i < 2 * COLS; ++i)
+            L.st_out[i] = kWave * i + lane < outs ? (uint32_t)(2 * c0 + kWave * i + lane) * cx.d_w : kOob;
+        L.stage_wr = stage + 2 * COLS * lane;
+        L.stage_rd = stage + 2 * HALO_L + lane;
+        // A branch that is always taken, which the compiler cannot know, ends
+        // a basic block at every row's stores.  In one block per trip, the
+        // lane shifts of a row are merged with the next row's equal ones into
+        // moves of their own instead of folding into additions as DPP operands
+        // (19 moves against 8 per row of two columns) and the stores sink past
+        // their row: 274 VGPRs against 168.
+        int one = 1;
+        asm volatile("" : "+s"(one));
+        L.split = one != 0;
+    }
 
     StripState<COLS> s;
 #pragma unroll
@@ -677,7 +681,7 @@ __device__ __forceinline__ void zoom_strip(const StripCtx& cx, const FwdParams& 
     // Main walk, several rows per trip so that values carried from row to row
     // are renamed rather than copied: six rows (the input windows span six
     // rows and the x-point windows three, so all of them rotate by renaming
-    // alone), two for the runtime-flag path and for the two-column byte-output
+    // alone), two for the two-column byte-output
     // kernels (six-row trips would need over 256 VGPRs there: one wave per
     // SIMD).  Measured VALU instructions per quad of the main loop: one
     // column, six-row trips 164-174 against 178-185 for two-row trips.  The
@@ -685,7 +689,7 @@ __device__ __forceinline__ void zoom_strip(const StripCtx& cx, const FwdParams& 
     // operations of a whole trip, as on every later trip, so the compiler's
     // wait counts for the queued loads are exact rather than those of the
     // store-free prologue.
-    constexpr int TRIP = (IO == kIoGeneric || (COLS == 2 && io_out_u8(IO))) ? 2 : 6;
+    constexpr int TRIP = COLS == 2 && io_out_u8(IO) ? 2 : 6;
     int R = R0;
     {
         const int q1 = R0 + (R1 - R0) / 4, q2 = R0 + (R1 - R0) / 2, q3 = R0 + 3 * (R1 - R0) / 4;
