@@ -39,7 +39,8 @@ ALU_PEAK_PACKED_TFLOPS = 157.2864
 # x point 74, each + point 64, second differences of phase 2 12
 FLOPS_PER_QUAD = 214
 KERNEL_SOURCES = ["paper_2312_00229_amd/csrc/weno_fwd.h",  # the forward kernel body
-                  "paper_2312_00229_amd/csrc/weno_api.hip"]  # its launch: grid, block map, strip shape
+                  "paper_2312_00229_amd/csrc/weno_zoom.hip",  # its launch: grid, block map
+                  "paper_2312_00229_amd/csrc/weno_api.hip"]  # its strip shape
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_zoom2x_rgb_f32_1080p.json")
 
 

@@ -10,13 +10,18 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libweno_zoom.so")
-SOURCES = ["weno_api.hip", "weno_bwd.hip", "weno_resample.hip"]
+# (source, macros, object name): the doubling's kernels compile once per I/O
+# mode (kIo* of weno_fwd.h), so that the compilations run side by side
+OBJECTS = [("weno_zoom.hip", ["-DWENO_IO=%d" % io], "weno_zoom%d" % io) for io in range(8)] + [
+    ("weno_api.hip", [], "weno_api"), ("weno_bwd.hip", [], "weno_bwd"), ("weno_resample.hip", [], "weno_resample")]
 ARCH = os.environ.get("WENO_OFFLOAD_ARCH", "gfx950")
 
 
@@ -27,27 +32,39 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found (ROCm is required to build the library)")
 
 
+DEVICE_FLAGS = ["--offload-arch=" + ARCH, "-std=c++17", "-fPIC", "-ffp-contract=off",
+                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-result",
+                "-I" + INCLUDE, "-I" + CSRC]
+
+
+def _compile(flags, out_dir, verbose):
+    """The objects of OBJECTS in out_dir, a few compilations at a time."""
+    jobs = int(os.environ.get("MAX_JOBS") or min(8, os.cpu_count() or 1))
+
+    def one(entry):
+        src, macros, name = entry
+        obj = os.path.join(out_dir, name + ".o")
+        cmd = [hipcc(), *flags, *DEVICE_FLAGS, *macros, "-c", os.path.join(CSRC, src), "-o", obj]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            sys.stderr.write(res.stdout + res.stderr)
+            raise RuntimeError("hipcc failed compiling %s" % src)
+        return obj
+
+    with ThreadPoolExecutor(max(1, jobs)) as pool:
+        return list(pool.map(one, OBJECTS))
+
+
 def build(verbose: bool = False) -> str:
-    srcs = [os.path.join(CSRC, s) for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
     tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [
-        hipcc(),
-        "--offload-arch=" + ARCH,
-        "-O3",
-        "-std=c++17",
-        "-fPIC",
-        "-shared",
-        "-ffp-contract=off",
-        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        "-Wno-unused-result",
-        "-I" + INCLUDE,
-        "-I" + CSRC,
-        *srcs,
-        "-o", tmp,
-    ]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
+    with tempfile.TemporaryDirectory() as objs_dir:
+        objs = _compile(["-O3"], objs_dir, verbose)
+        cmd = [hipcc(), "--offload-arch=" + ARCH, "-shared", "-fPIC", *objs, "-o", tmp]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc failed building %s" % LIB)
@@ -57,26 +74,11 @@ def build(verbose: bool = False) -> str:
 
 def build_asan(out_dir: str, verbose: bool = False) -> str:
     """The same library with AddressSanitizer on its HOST code only (device
-    code is built as usual), for the ABI checks on the CPU: the three sources
-    are compiled in parallel and linked into out_dir/libweno_zoom_asan.so.
-    Load it through WENO_ZOOM_LIB with the sanitizer runtime preloaded
-    (asan_runtime())."""
+    code is built as usual), for the ABI checks on the CPU, linked into
+    out_dir/libweno_zoom_asan.so.  Load it through WENO_ZOOM_LIB with the
+    sanitizer runtime preloaded (asan_runtime())."""
     os.makedirs(out_dir, exist_ok=True)
-    common = [hipcc(), "--offload-arch=" + ARCH, "-O1", "-g", "-std=c++17", "-fPIC", "-fno-omit-frame-pointer",
-              "-Xarch_host", "-fsanitize=address",
-              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-result",
-              "-I" + INCLUDE, "-I" + CSRC]
-    objs, procs = [], []
-    for src in SOURCES:
-        obj = os.path.join(out_dir, src.replace(".hip", ".o"))
-        objs.append(obj)
-        procs.append(subprocess.Popen(common + ["-c", os.path.join(CSRC, src), "-o", obj],
-                                      stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))
-    for pr in procs:
-        out, _ = pr.communicate()
-        if pr.returncode != 0:
-            sys.stderr.write(out)
-            raise RuntimeError("hipcc failed building the sanitizer objects")
+    objs = _compile(["-O1", "-g", "-fno-omit-frame-pointer", "-Xarch_host", "-fsanitize=address"], out_dir, verbose)
     lib = os.path.join(out_dir, "libweno_zoom_asan.so")
     cmd = [hipcc(), "--offload-arch=" + ARCH, "-shared", "-fPIC", "-Xarch_host", "-fsanitize=address", *objs,
            "-o", lib]

@@ -1,6 +1,7 @@
 // C ABI of the WD-WENO 2x zoom library (declarations and contracts in
 // include/weno_zoom.h).  Host-side validation, launch configuration and the
-// forward / batched / cascade kernels; the adjoint lives in weno_bwd.hip.
+// batched and cascade entry points; the doubling's kernels live in
+// weno_zoom.hip, the adjoint in weno_bwd.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -19,166 +20,11 @@
 
 using namespace wz;
 
-// --------------------------------------------------------------------------
-// kernels
-// --------------------------------------------------------------------------
 namespace {
-
-// per-plane context: buffer resources over the plane's byte extent
-__device__ __forceinline__ StripCtx make_ctx(const FwdJob& jb, int n, int c, float out_scale)
-{
-    StripCtx cx;
-    cx.src = make_rsrc(jb.src + n * jb.s_n + c * jb.s_c, jb.src_extent);
-    cx.dst = make_rsrc(jb.dst + n * jb.d_n + c * jb.d_c, jb.dst_extent);
-    cx.s_h = (uint32_t)jb.s_h;
-    cx.s_w_bytes = (uint32_t)jb.s_w;
-    cx.d_h = (uint32_t)jb.d_h;
-    cx.d_w = (uint32_t)jb.d_w;
-    cx.H = jb.H;
-    cx.W = jb.W;
-    cx.src_shift = jb.src_shift;
-    cx.src_h = jb.src_h;
-    cx.src_w = jb.src_w;
-    cx.out_scale = out_scale;
-    return cx;
-}
-
-// TAIL (two columns only): the launch has one-column tail strips
-// (jb.tail_rows > 0) and one wave index across the planes
-// Two-column kernels are held to 168 VGPRs, three waves per SIMD: strided float
-// destinations would take 170 (two to four values spill).
-template <int COLS, int BETA, int IO, bool PACED, bool TAIL = false>
-__global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJob jb, FwdParams P, int rows_per_strip)
-{
-    // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.
-    // Renumber them so that every XCD gets a contiguous range of strips
-    // (whole bands of adjacent rows): the 9 halo rows a strip shares with the
-    // strip above are then re-read from the same L2.  A bijection on
-    // [0, gridDim.x).  The XCD of a workgroup is its linear index (plane-major)
-    // mod 8, so the XCD of a strip rotates from plane to plane, which spreads
-    // the planes' workgroups evenly over the XCDs.  With tail strips the grid
-    // is one-dimensional and every XCD gets a contiguous range of waves, plane
-    // after plane.  For images whose planes are interleaved (HWC) the grid is
-    // one-dimensional too, a multiple of 8 workgroups per plane, and on each
-    // XCD a strip's workgroups of all the planes follow each other: the lines
-    // the planes share meet in one L2 while they are there, instead of reaching
-    // HBM once per plane with a third of their bytes each (1080p RGB uint8:
-    // writes 3.0x -> 1.0x the output, reads 4.1x -> 1.1x the input).
-    const int nb = gridDim.x, b = blockIdx.x;
-    const int xcd = b % kXcds, k = b / kXcds;
-    const int logical = xcd * (nb / kXcds) + min(xcd, nb % kXcds) + k;
-    // the wave index is the same in every lane; say so, so that strip rows and
-    // buffer offsets live in SGPRs
-    const int wave = __builtin_amdgcn_readfirstlane(logical * kWavesPerBlock + (threadIdx.x >> 6));
-    float* stage = nullptr;
-    if constexpr (stage_floats<COLS, IO>() > 0) {
-        __shared__ float rows[kWavesPerBlock * stage_floats<COLS, IO>()];
-        stage = rows + (threadIdx.x >> 6) * stage_floats<COLS, IO>();
-    }
-    if constexpr (TAIL) {
-        // One wave index across the planes (gridDim.y is 1).  Per plane: the
-        // two-column strips, band by band, then the one-column strips of the
-        // last columns (no more than a one-column strip owns), whose bands
-        // are taller so that each walks about as long as a two-column strip.
-        static_assert(COLS == 2, "tail strips follow two-column strips");
-        const int n2 = jb.strips_x * jb.strips_y, per_plane = n2 + jb.tail_bands;
-        const int plane = wave / per_plane;
-        if (plane >= jb.planes) return;  // whole wave
-        const int w = wave - plane * per_plane;
-        const int n = plane / jb.C, c = plane - n * jb.C;
-        const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
-        if (w < n2) {
-            const int sy = w / jb.strips_x, sx = w - sy * jb.strips_x;
-            const int R0 = sy * rows_per_strip;
-            zoom_strip<2, BETA, IO, PACED>(cx, P, sx * strip_own<2>(), R0, min(R0 + rows_per_strip, jb.H),
-                                           stage);
-        } else {
-            const int R0 = (w - n2) * jb.tail_rows;
-            zoom_strip<1, BETA, IO, PACED>(cx, P, jb.strips_x * strip_own<2>(), R0, min(R0 + jb.tail_rows, jb.H),
-                                           stage);
-        }
-    } else {
-        int n, c, w = wave;
-        if (jb.share) {
-            // on each XCD: image by image, workgroup by workgroup, plane by plane
-            const int per_xcd = nb / (kXcds * jb.planes);
-            n = k / (per_xcd * jb.C);
-            const int r = k - n * per_xcd * jb.C;
-            c = r % jb.C;
-            w = __builtin_amdgcn_readfirstlane((xcd * per_xcd + r / jb.C) * kWavesPerBlock + (threadIdx.x >> 6));
-        } else {
-            n = blockIdx.y / jb.C;
-            c = blockIdx.y - n * jb.C;
-        }
-        if (w >= jb.strips_x * jb.strips_y) return;  // whole wave
-        const int sy = w / jb.strips_x;
-        const int sx = w - sy * jb.strips_x;
-        const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
-        const int R0 = sy * rows_per_strip;
-        const int R1 = min(R0 + rows_per_strip, jb.H);
-        zoom_strip<COLS, BETA, IO, PACED>(cx, P, sx * strip_own<COLS>(), R0, R1, stage);
-    }
-}
-
-// Persistent kernel over a work queue of strips of many images.  Item i of
-// image k covers plane (i / per_plane) and strip (i % per_plane); images are
-// stored in the table largest first, so the queue drains big items early.
-// The table is read-only during the launch and the queue head is reached
-// through its own pointer, so table reads compile to scalar loads.
-template <int COLS, int BETA>
-__global__ __launch_bounds__(kBlock) void zoom2x_batched_kernel(const BatchTable* __restrict__ tab,
-                                                                unsigned long long* __restrict__ counter,
-                                                                int rows_per_strip)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int count = tab->count;
-    const int64_t total = tab->total_items;
-    const FwdJob* __restrict__ jobs = batch_jobs(tab);
-    const int64_t* __restrict__ prefix = batch_prefix(tab);
-    __shared__ float rows[kWavesPerBlock * stage_floats<COLS, kIoF32S>()];
-    float* const stage = rows + (threadIdx.x >> 6) * stage_floats<COLS, kIoF32S>();
-    for (;;) {
-        unsigned long long got = 0;
-        if (lane == 0) got = atomicAdd(counter, 1ull);
-        // broadcast lane 0's ticket as a provably uniform (scalar) value, so the
-        // image table is read with scalar loads and the buffer resources stay
-        // in SGPRs
-        const uint32_t lo32 = __builtin_amdgcn_readfirstlane((uint32_t)got);
-        const uint32_t hi32 = __builtin_amdgcn_readfirstlane((uint32_t)(got >> 32));
-        const unsigned long long item = ((unsigned long long)hi32 << 32) | lo32;
-        if ((int64_t)item >= total) break;  // every wave reaches this exit
-        // image k with prefix[k] <= item < prefix[k+1]
-        int lo = 0, hi = count - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (prefix[mid] <= (int64_t)item) lo = mid; else hi = mid - 1;
-        }
-        const FwdJob jb = jobs[lo];
-        const int64_t local = (int64_t)item - prefix[lo];
-        const int per_plane = jb.strips_x * jb.strips_y;
-        const int plane = (int)(local / per_plane);
-        const int wv = (int)(local - (int64_t)plane * per_plane);
-        const int sy = wv / jb.strips_x;
-        const int sx = wv - sy * jb.strips_x;
-        const int n = plane / jb.C, c = plane - n * jb.C;
-        const FwdParams P = batch_params(tab)[lo];
-        const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
-        const int R0 = sy * rows_per_strip;
-        const int R1 = min(R0 + rows_per_strip, jb.H);
-        switch (jb.io) {
-        case kIoF32: zoom_strip<COLS, BETA, kIoF32>(cx, P, sx * strip_own<COLS>(), R0, R1); break;
-        case kIoU8: zoom_strip<COLS, BETA, kIoU8>(cx, P, sx * strip_own<COLS>(), R0, R1); break;
-        case kIoU8F32: zoom_strip<COLS, BETA, kIoU8F32>(cx, P, sx * strip_own<COLS>(), R0, R1); break;
-        case kIoF32U8: zoom_strip<COLS, BETA, kIoF32U8>(cx, P, sx * strip_own<COLS>(), R0, R1); break;
-        case kIoF32S: zoom_strip<COLS, BETA, kIoF32S>(cx, P, sx * strip_own<COLS>(), R0, R1, stage); break;
-        default: zoom_strip<COLS, BETA, kIoU8F32S>(cx, P, sx * strip_own<COLS>(), R0, R1, stage); break;
-        }
-    }
-}
 
 __global__ void reset_counter_kernel(BatchTable* tab)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) tab->counter = 0ull;
+    if (threadIdx.x < kIoModes) tab->counter[threadIdx.x] = 0ull;
 }
 
 }  // namespace
@@ -385,12 +231,13 @@ FwdJob wz_make_job(const weno_tensor_t* src, const weno_tensor_t* dst, int cols,
         jb.tail_bands = (src->h + tail_rows - 1) / tail_rows;
     }
     jb.share = planes_share_lines(jb.C, jb.s_c, jb.s_h) || planes_share_lines(jb.C, jb.d_c, jb.d_h);
-    // vector stores need contiguous columns and 4-byte aligned elements (what
-    // a float tensor has)
-    const bool vec_rows = dst->sw == 1 && (uintptr_t)dst->data % 4 == 0;
-    if (jb.out_u8) jb.io = jb.in_u8 ? kIoU8 : kIoF32U8;
-    else if (vec_rows) jb.io = jb.in_u8 ? kIoU8F32 : kIoF32;
-    else jb.io = jb.in_u8 ? kIoU8F32S : kIoF32S;
+    // A lane's outputs are stored together where the columns are contiguous.
+    // Float rows are 4-byte aligned, which is all a vector store needs (a
+    // pointer that is not takes element stores); packed bytes go out as one
+    // word at any alignment, which this architecture allows buffer stores.
+    const bool rows_ok = dst->sw == 1 && (jb.out_u8 || (uintptr_t)dst->data % 4 == 0);
+    if (jb.out_u8) jb.io = jb.in_u8 ? (rows_ok ? kIoU8 : kIoU8S) : (rows_ok ? kIoF32U8 : kIoF32U8S);
+    else jb.io = jb.in_u8 ? (rows_ok ? kIoU8F32 : kIoU8F32S) : (rows_ok ? kIoF32 : kIoF32S);
     jb.dst_extent = (uint32_t)wz_plane_extent(dst);
     weno_tensor_t region;
     wz_source_region(src, boundary, &region);   // validated by the caller
@@ -431,85 +278,8 @@ int wz_check_pair(const weno_tensor_t* src, const weno_tensor_t* dst, int factor
     return WENO_OK;
 }
 
-static int device_cus();
-
-// Workgroups of a kernel that one compute unit holds at once.  Cached per
-// kernel: it depends only on the kernel's registers and the architecture,
-// and the library is built for one architecture.
-template <int COLS, int BETA, int IO>
-static int fwd_resident_blocks()
-{
-    static std::atomic<int> cache{0};
-    int v = cache.load();
-    if (v == 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &v, reinterpret_cast<const void*>(zoom2x_kernel<COLS, BETA, IO, true>), kBlock, 0) != hipSuccess ||
-            v <= 0)
-            v = 1;
-        cache.store(v);
-    }
-    return v;
-}
-
-// Workgroups of a plane of `strips` strips: padded to a multiple of the XCD
-// count when the planes share lines (zoom2x_kernel), the padding exiting at
-// once.  The busiest XCD then holds planes x grid_x / 8 of them.
-static int fwd_grid_x(int64_t strips, bool share)
-{
-    const int64_t bx = (strips + kWavesPerBlock - 1) / kWavesPerBlock;
-    return (int)(share ? (bx + kXcds - 1) / kXcds * kXcds : bx);
-}
-
-// A launch whose workgroups all fit on the device at once (one round) is
-// paced (zoom_strip); one of several rounds is not.
-template <int COLS, int BETA, int IO>
-static hipError_t launch_fwd_beta(const FwdJob& jb, const FwdParams& P, int rows, hipStream_t st)
-{
-    dim3 grid(fwd_grid_x((int64_t)jb.strips_x * jb.strips_y, jb.share), jb.planes);
-    if (jb.share) grid = dim3(grid.x * grid.y, 1);   // the planes' workgroups interleaved (zoom2x_kernel)
-    if constexpr (COLS == 2) {
-        if (jb.tail_rows > 0) {  // one wave index across the planes
-            const int64_t waves = (int64_t)jb.planes * ((int64_t)jb.strips_x * jb.strips_y + jb.tail_bands);
-            grid = dim3((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock), 1);
-            if ((int64_t)grid.x <= (int64_t)fwd_resident_blocks<COLS, BETA, IO>() * device_cus())
-                hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, true, true>), grid, dim3(kBlock), 0, st, jb, P, rows);
-            else
-                hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, false, true>), grid, dim3(kBlock), 0, st, jb, P,
-                                   rows);
-            return hipGetLastError();
-        }
-    }
-    const int64_t blocks = (int64_t)grid.x * grid.y;
-    if (blocks <= (int64_t)fwd_resident_blocks<COLS, BETA, IO>() * device_cus())
-        hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, true>), grid, dim3(kBlock), 0, st, jb, P, rows);
-    else
-        hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, false>), grid, dim3(kBlock), 0, st, jb, P, rows);
-    return hipGetLastError();
-}
-
-template <int COLS, int IO>
-static hipError_t launch_fwd_io(const FwdJob& jb, const FwdParams& P, int beta_mode, int rows, hipStream_t st)
-{
-    if (beta_mode == 2) return launch_fwd_beta<COLS, 2, IO>(jb, P, rows, st);
-    if (beta_mode == 1) return launch_fwd_beta<COLS, 1, IO>(jb, P, rows, st);
-    return launch_fwd_beta<COLS, kBetaGeneral, IO>(jb, P, rows, st);
-}
-
-template <int COLS>
-static hipError_t launch_fwd_cols(const FwdJob& jb, const FwdParams& P, int beta_mode, int rows, hipStream_t st)
-{
-    switch (jb.io) {
-    case kIoF32: return launch_fwd_io<COLS, kIoF32>(jb, P, beta_mode, rows, st);
-    case kIoU8: return launch_fwd_io<COLS, kIoU8>(jb, P, beta_mode, rows, st);
-    case kIoU8F32: return launch_fwd_io<COLS, kIoU8F32>(jb, P, beta_mode, rows, st);
-    case kIoF32U8: return launch_fwd_io<COLS, kIoF32U8>(jb, P, beta_mode, rows, st);
-    case kIoF32S: return launch_fwd_io<COLS, kIoF32S>(jb, P, beta_mode, rows, st);
-    default: return launch_fwd_io<COLS, kIoU8F32S>(jb, P, beta_mode, rows, st);
-    }
-}
-
 // compute units of the current device, cached per device
-static int device_cus()
+int wz_device_cus()
 {
     static std::atomic<int> cache[64];
     int dev = 0;
@@ -558,7 +328,7 @@ constexpr int kTailStretch = 7;
 
 void wz_auto_config(int64_t planes, int H, int W, bool share, int* rows, int* cols, int* tail_rows)
 {
-    const int64_t cus = device_cus();
+    const int64_t cus = wz_device_cus();
     double best = 0.0;
     int best_rows = 8, best_cols = 2, best_tail = 0;
     for (int c = 2; c >= 1; --c) {
@@ -573,7 +343,7 @@ void wz_auto_config(int64_t planes, int H, int W, bool share, int* rows, int* co
             if (bands < 1) bands = 1;
             int r = (int)((H + bands - 1) / bands);
             r = r < 4 ? 4 : (r > 4096 ? 4096 : r);
-            const int64_t blocks = planes * fwd_grid_x(strips_x * ((H + r - 1) / r), share);
+            const int64_t blocks = planes * wz_grid_x(strips_x * ((H + r - 1) / r), share);
             const int64_t mm = (blocks + cus - 1) / cus;
             const double cost = (double)mm * (r + kStartCost) * iteration_cost(c, mm);
             if (best == 0.0 || cost < best) {
@@ -622,9 +392,17 @@ void wz_config_for(const weno_tensor_t* src, const weno_tensor_t* dst, int* rows
     *cols = g_cols_per_lane.load();
     *tail_rows = 0;
     const bool share = planes_share_lines(src->c, src->sc, src->sh) || planes_share_lines(dst->c, dst->sc, dst->sh);
-    if (*rows == 0 || *cols == 0)
+    if (*rows == 0 || *cols == 0) {
         wz_auto_config((int64_t)src->n * src->c, src->h, src->w, share, rows, cols, tail_rows);
+        if (dst->sw != 1) *tail_rows = 0;   // tail strips store contiguous columns only
+    }
 }
+
+// the launchers of each I/O mode (weno_zoom.hip)
+static const ZoomLauncher kZoomLaunchers[kIoModes] = {
+    zoom_launcher<0>(), zoom_launcher<1>(), zoom_launcher<2>(), zoom_launcher<3>(),
+    zoom_launcher<4>(), zoom_launcher<5>(), zoom_launcher<6>(), zoom_launcher<7>(),
+};
 
 int wz_launch_fwd(const weno_tensor_t* src, const weno_tensor_t* dst, const weno_params_t* p, hipStream_t st,
                   int rows, int cols, int tail_rows)
@@ -632,7 +410,7 @@ int wz_launch_fwd(const weno_tensor_t* src, const weno_tensor_t* dst, const weno
     const FwdJob jb = wz_make_job(src, dst, cols, rows, p->boundary, tail_rows);
     const FwdParams P = wz_fwd_params(p, jb.in_u8, jb.out_u8);
     const int bm = wz_beta_mode(p->beta);
-    const hipError_t e = cols == 1 ? launch_fwd_cols<1>(jb, P, bm, rows, st) : launch_fwd_cols<2>(jb, P, bm, rows, st);
+    const hipError_t e = kZoomLaunchers[jb.io].single(jb, P, bm, cols, rows, st);
     if (e != hipSuccess) return wz_hip_error(e, "zoom2x_kernel launch");
     return WENO_OK;
 }
@@ -733,30 +511,37 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
         rows = 32;
         cols = 2;
     }
-    // largest images first
+    // by I/O mode (each has a queue of its own), then largest images first
+    std::vector<FwdJob> made(count);
     std::vector<int> order(count);
-    for (int i = 0; i < count; ++i) order[i] = i;
+    for (int i = 0; i < count; ++i) {
+        made[i] = wz_make_job(&srcs[i], &dsts[i], cols, rows, p->boundary, 0);
+        order[i] = i;
+    }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        return (int64_t)srcs[a].h * srcs[a].w * srcs[a].n * srcs[a].c >
-               (int64_t)srcs[b].h * srcs[b].w * srcs[b].n * srcs[b].c;
+        const FwdJob &A = made[a], &B = made[b];
+        if (A.io != B.io) return A.io < B.io;
+        return (int64_t)A.H * A.W * A.planes > (int64_t)B.H * B.W * B.planes;
     });
     std::vector<uint8_t> host(batch_table_bytes(count), 0);
     BatchTable* tab = (BatchTable*)host.data();
     FwdJob* jobs = (FwdJob*)(host.data() + batch_jobs_offset());
     int64_t* prefix = (int64_t*)(host.data() + batch_prefix_offset(count));
     FwdParams* prm = (FwdParams*)(host.data() + batch_params_offset(count));
-    int64_t total = 0;
+    int64_t total = 0, modes = 0;
+    int io = 0;   // queues [0, io] have their first item
     for (int k = 0; k < count; ++k) {
-        const int i = order[k];
-        jobs[k] = wz_make_job(&srcs[i], &dsts[i], cols, rows, p->boundary, 0);
+        jobs[k] = made[order[k]];
+        while (io < jobs[k].io) tab->first[++io] = total;
+        modes |= 1ll << io;
         prm[k] = wz_fwd_params(p, jobs[k].in_u8, jobs[k].out_u8);
         prefix[k] = total;
         total += (int64_t)jobs[k].planes * jobs[k].strips_x * jobs[k].strips_y;
     }
     prefix[count] = total;
+    while (io < kIoModes) tab->first[++io] = total;
     tab->count = count;
     tab->total_items = total;
-    tab->counter = 0;
     tab->params_offset = batch_params_offset(count);
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e = hipMemcpyAsync(d_workspace, host.data(), host.size(), hipMemcpyHostToDevice, st);
@@ -770,34 +555,8 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
     plan->rows_per_strip = rows;
     plan->cols_per_lane = cols;
     plan->beta_mode = wz_beta_mode(p->beta);
-    plan->reserved = 0;
+    plan->reserved = modes;
     return WENO_OK;
-}
-
-template <int COLS>
-static hipError_t launch_batched_cols(const weno_batch_plan_t* plan, hipStream_t st)
-{
-    const int cus = device_cus();
-    const int64_t waves_needed = plan->total_items;
-    int64_t blocks = (int64_t)cus * 4;  // up to 4 workgroups (16 waves) per CU
-    const int64_t by_work = (waves_needed + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (blocks > by_work) blocks = by_work;
-    if (blocks < 1) blocks = 1;
-    const BatchTable* tab = (const BatchTable*)plan->d_workspace;
-    unsigned long long* counter = &((BatchTable*)plan->d_workspace)->counter;
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, (BatchTable*)plan->d_workspace);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (plan->beta_mode == 2)
-        hipLaunchKernelGGL((zoom2x_batched_kernel<COLS, 2>), dim3((unsigned)blocks), dim3(kBlock), 0, st, tab,
-                           counter, plan->rows_per_strip);
-    else if (plan->beta_mode == 1)
-        hipLaunchKernelGGL((zoom2x_batched_kernel<COLS, 1>), dim3((unsigned)blocks), dim3(kBlock), 0, st, tab,
-                           counter, plan->rows_per_strip);
-    else
-        hipLaunchKernelGGL((zoom2x_batched_kernel<COLS, kBetaGeneral>), dim3((unsigned)blocks), dim3(kBlock), 0, st,
-                           tab, counter, plan->rows_per_strip);
-    return hipGetLastError();
 }
 
 extern "C" int weno_zoom2x_batched_run(const weno_batch_plan_t* plan, void* hip_stream)
@@ -805,8 +564,15 @@ extern "C" int weno_zoom2x_batched_run(const weno_batch_plan_t* plan, void* hip_
     if (!plan || !plan->d_workspace || plan->count < 1 || plan->total_items < 1) return WENO_EINVAL;
     if (plan->cols_per_lane != 1 && plan->cols_per_lane != 2) return WENO_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
-    const hipError_t e = plan->cols_per_lane == 1 ? launch_batched_cols<1>(plan, st) : launch_batched_cols<2>(plan, st);
-    if (e != hipSuccess) return wz_hip_error(e, "zoom2x_batched_kernel launch");
+    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, (BatchTable*)plan->d_workspace);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return wz_hip_error(e, "reset_counter_kernel launch");
+    // one launch per I/O mode among the images, nearly always one in all
+    for (int io = 0; io < kIoModes; ++io) {
+        if (!((plan->reserved >> io) & 1)) continue;
+        e = kZoomLaunchers[io].batched(plan, st);
+        if (e != hipSuccess) return wz_hip_error(e, "zoom2x_batched_kernel launch");
+    }
     return WENO_OK;
 }
 

@@ -11,16 +11,19 @@
 // Device-resident table of a batched call, written into the caller's
 // workspace by weno_zoom2x_batched_plan:
 //   [0, 256)                 BatchTable header
-//   [256, ...)               FwdJob jobs[count]       (largest image first)
+//   [256, ...)               FwdJob jobs[count]       (by I/O mode, then largest image first)
 //   then                     int64_t prefix[count+1]  (first queue item of each image)
 //   then                     FwdParams params[count]
 struct BatchTable {
-    unsigned long long counter;  // queue head, zeroed by a kernel before every run
+    unsigned long long counter[wz::kIoModes];  // queue head per I/O mode, zeroed by a kernel before every run
+    int64_t first[wz::kIoModes + 1];           // items of mode m: [first[m], first[m + 1])
     int64_t total_items;
     int32_t count;
     int32_t pad0;
     int64_t params_offset;
 };
+
+static_assert(sizeof(BatchTable) <= 256, "the jobs start at byte 256");
 
 __host__ __device__ constexpr size_t batch_jobs_offset() { return 256; }
 __host__ __device__ constexpr size_t batch_prefix_offset(int count)
@@ -59,3 +62,25 @@ bool wz_overlap(const weno_tensor_t* a, const weno_tensor_t* b);
 int64_t wz_plane_extent(const weno_tensor_t* t);
 double wz_nbw(const weno_params_t* p);
 int wz_beta_mode(float beta);
+int wz_device_cus();
+
+// Workgroups of a plane of `strips` strips: padded to a multiple of the XCD
+// count when the planes share lines (zoom2x_kernel), the padding exiting at
+// once.  The busiest XCD then holds planes x grid_x / 8 of them.
+inline int wz_grid_x(int64_t strips, bool share)
+{
+    using namespace wz;
+    const int64_t bx = (strips + kWavesPerBlock - 1) / kWavesPerBlock;
+    return (int)(share ? (bx + kXcds - 1) / kXcds * kXcds : bx);
+}
+
+// Launches of one I/O mode (weno_zoom.hip, compiled once per mode): one doubling
+// of a job with its beta mode, columns per lane and strip height, and a batch
+// plan's images of that mode.
+struct ZoomLauncher {
+    hipError_t (*single)(const wz::FwdJob& jb, const wz::FwdParams& P, int beta_mode, int cols, int rows,
+                         hipStream_t st);
+    hipError_t (*batched)(const weno_batch_plan_t* plan, hipStream_t st);
+};
+template <int IO>
+ZoomLauncher zoom_launcher();

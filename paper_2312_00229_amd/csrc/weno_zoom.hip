@@ -1,0 +1,264 @@
+// The doubling's kernels and their launches, one object per I/O mode: this file
+// is compiled once for each value of WENO_IO (kIo* of weno_fwd.h).
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+
+#include "weno_fwd.h"
+#include "weno_internal.h"
+#include "weno_zoom.h"
+
+#ifndef WENO_IO
+#error "compile with -DWENO_IO=<I/O mode>"
+#endif
+
+using namespace wz;
+
+namespace {
+
+// per-plane context: buffer resources over the plane's byte extent
+__device__ __forceinline__ StripCtx make_ctx(const FwdJob& jb, int n, int c, float out_scale)
+{
+    StripCtx cx;
+    cx.src = make_rsrc(jb.src + n * jb.s_n + c * jb.s_c, jb.src_extent);
+    cx.dst = make_rsrc(jb.dst + n * jb.d_n + c * jb.d_c, jb.dst_extent);
+    cx.s_h = (uint32_t)jb.s_h;
+    cx.s_w_bytes = (uint32_t)jb.s_w;
+    cx.d_h = (uint32_t)jb.d_h;
+    cx.d_w = (uint32_t)jb.d_w;
+    cx.H = jb.H;
+    cx.W = jb.W;
+    cx.src_shift = jb.src_shift;
+    cx.src_h = jb.src_h;
+    cx.src_w = jb.src_w;
+    cx.out_scale = out_scale;
+    return cx;
+}
+
+// this wave's LDS rows for staged stores
+template <int COLS, int IO>
+__device__ __forceinline__ float* wave_stage()
+{
+    if constexpr (io_out_staged(IO)) {
+        __shared__ __align__(16) float rows[kWavesPerBlock * stage_floats<COLS, IO>()];
+        return rows + (threadIdx.x >> 6) * stage_floats<COLS, IO>();
+    } else {
+        return nullptr;
+    }
+}
+
+// TAIL (two columns only): the launch has one-column tail strips
+// (jb.tail_rows > 0) and one wave index across the planes
+// Two-column kernels are held to 168 VGPRs, three waves per SIMD: strided float
+// destinations would take 170 (two to four values spill).
+template <int COLS, int BETA, int IO, bool PACED, bool TAIL = false>
+__global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJob jb, FwdParams P, int rows_per_strip)
+{
+    // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.
+    // Renumber them so that every XCD gets a contiguous range of strips
+    // (whole bands of adjacent rows): the 9 halo rows a strip shares with the
+    // strip above are then re-read from the same L2.  A bijection on
+    // [0, gridDim.x).  The XCD of a workgroup is its linear index (plane-major)
+    // mod 8, so the XCD of a strip rotates from plane to plane, which spreads
+    // the planes' workgroups evenly over the XCDs.  With tail strips the grid
+    // is one-dimensional and every XCD gets a contiguous range of waves, plane
+    // after plane.  For images whose planes are interleaved (HWC) the grid is
+    // one-dimensional too, a multiple of 8 workgroups per plane, and on each
+    // XCD a strip's workgroups of all the planes follow each other: the lines
+    // the planes share meet in one L2 while they are there, instead of reaching
+    // HBM once per plane with a third of their bytes each (1080p RGB uint8:
+    // writes 3.0x -> 1.0x the output, reads 4.1x -> 1.1x the input).
+    const int nb = gridDim.x, b = blockIdx.x;
+    const int xcd = b % kXcds, k = b / kXcds;
+    const int logical = xcd * (nb / kXcds) + min(xcd, nb % kXcds) + k;
+    // the wave index is the same in every lane; say so, so that strip rows and
+    // buffer offsets live in SGPRs
+    const int wave = __builtin_amdgcn_readfirstlane(logical * kWavesPerBlock + (threadIdx.x >> 6));
+    float* const stage = wave_stage<COLS, IO>();
+    if constexpr (TAIL) {
+        // One wave index across the planes (gridDim.y is 1).  Per plane: the
+        // two-column strips, band by band, then the one-column strips of the
+        // last columns (no more than a one-column strip owns), whose bands
+        // are taller so that each walks about as long as a two-column strip.
+        static_assert(COLS == 2, "tail strips follow two-column strips");
+        const int n2 = jb.strips_x * jb.strips_y, per_plane = n2 + jb.tail_bands;
+        const int plane = wave / per_plane;
+        if (plane >= jb.planes) return;  // whole wave
+        const int w = wave - plane * per_plane;
+        const int n = plane / jb.C, c = plane - n * jb.C;
+        const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
+        if (w < n2) {
+            const int sy = w / jb.strips_x, sx = w - sy * jb.strips_x;
+            const int R0 = sy * rows_per_strip;
+            zoom_strip<2, BETA, IO, PACED>(cx, P, sx * strip_own<2>(), R0, min(R0 + rows_per_strip, jb.H),
+                                           stage);
+        } else {
+            const int R0 = (w - n2) * jb.tail_rows;
+            zoom_strip<1, BETA, IO, PACED>(cx, P, jb.strips_x * strip_own<2>(), R0, min(R0 + jb.tail_rows, jb.H),
+                                           stage);
+        }
+    } else {
+        int n, c, w = wave;
+        if (jb.share) {
+            // on each XCD: image by image, workgroup by workgroup, plane by plane
+            const int per_xcd = nb / (kXcds * jb.planes);
+            n = k / (per_xcd * jb.C);
+            const int r = k - n * per_xcd * jb.C;
+            c = r % jb.C;
+            w = __builtin_amdgcn_readfirstlane((xcd * per_xcd + r / jb.C) * kWavesPerBlock + (threadIdx.x >> 6));
+        } else {
+            n = blockIdx.y / jb.C;
+            c = blockIdx.y - n * jb.C;
+        }
+        if (w >= jb.strips_x * jb.strips_y) return;  // whole wave
+        const int sy = w / jb.strips_x;
+        const int sx = w - sy * jb.strips_x;
+        const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
+        const int R0 = sy * rows_per_strip;
+        const int R1 = min(R0 + rows_per_strip, jb.H);
+        zoom_strip<COLS, BETA, IO, PACED>(cx, P, sx * strip_own<COLS>(), R0, R1, stage);
+    }
+}
+
+// Persistent kernel over a work queue of strips of many images, those of one
+// I/O mode (a kernel that switched between all modes took the registers of the
+// largest: 176 VGPRs, two waves per SIMD).  Item i of image k covers plane (i / per_plane) and strip (i % per_plane); images are
+// stored in the table largest first, so the queue drains big items early.
+// The table is read-only during the launch and the queue head is reached
+// through its own pointer, so table reads compile to scalar loads.
+template <int COLS, int BETA, int IO>
+__global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_batched_kernel(const BatchTable* __restrict__ tab,
+                                                                                 unsigned long long* __restrict__ counter,
+                                                                                 int rows_per_strip)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int count = tab->count;
+    const int64_t first = tab->first[IO], total = tab->first[IO + 1];   // this mode's items
+    const FwdJob* __restrict__ jobs = batch_jobs(tab);
+    const int64_t* __restrict__ prefix = batch_prefix(tab);
+    float* const stage = wave_stage<COLS, IO>();
+    for (;;) {
+        unsigned long long got = 0;
+        if (lane == 0) got = atomicAdd(counter, 1ull);
+        // broadcast lane 0's ticket as a provably uniform (scalar) value, so the
+        // image table is read with scalar loads and the buffer resources stay
+        // in SGPRs
+        const uint32_t lo32 = __builtin_amdgcn_readfirstlane((uint32_t)got);
+        const uint32_t hi32 = __builtin_amdgcn_readfirstlane((uint32_t)(got >> 32));
+        const int64_t item = first + (int64_t)(((unsigned long long)hi32 << 32) | lo32);
+        if (item >= total) break;  // every wave reaches this exit
+        // image k with prefix[k] <= item < prefix[k+1]
+        int lo = 0, hi = count - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (prefix[mid] <= item) lo = mid; else hi = mid - 1;
+        }
+        const FwdJob jb = jobs[lo];
+        const int64_t local = item - prefix[lo];
+        const int per_plane = jb.strips_x * jb.strips_y;
+        const int plane = (int)(local / per_plane);
+        const int wv = (int)(local - (int64_t)plane * per_plane);
+        const int sy = wv / jb.strips_x;
+        const int sx = wv - sy * jb.strips_x;
+        const int n = plane / jb.C, c = plane - n * jb.C;
+        const FwdParams P = batch_params(tab)[lo];
+        const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
+        const int R0 = sy * rows_per_strip;
+        const int R1 = min(R0 + rows_per_strip, jb.H);
+        zoom_strip<COLS, BETA, IO>(cx, P, sx * strip_own<COLS>(), R0, R1, stage);
+    }
+}
+
+// Workgroups of a kernel that one compute unit holds at once.  Cached per
+// kernel: it depends only on the kernel's registers and the architecture,
+// and the library is built for one architecture.
+template <int COLS, int BETA, int IO>
+int resident_blocks()
+{
+    static std::atomic<int> cache{0};
+    int v = cache.load();
+    if (v == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &v, reinterpret_cast<const void*>(zoom2x_kernel<COLS, BETA, IO, true>), kBlock, 0) != hipSuccess ||
+            v <= 0)
+            v = 1;
+        cache.store(v);
+    }
+    return v;
+}
+
+// A launch whose workgroups all fit on the device at once (one round) is
+// paced (zoom_strip); one of several rounds is not.
+template <int COLS, int BETA, int IO>
+hipError_t launch_single(const FwdJob& jb, const FwdParams& P, int rows, hipStream_t st)
+{
+    dim3 grid(wz_grid_x((int64_t)jb.strips_x * jb.strips_y, jb.share), jb.planes);
+    if (jb.share) grid = dim3(grid.x * grid.y, 1);   // the planes' workgroups interleaved (zoom2x_kernel)
+    if constexpr (COLS == 2 && !io_out_spread(IO)) {
+        if (jb.tail_rows > 0) {  // one wave index across the planes
+            const int64_t waves = (int64_t)jb.planes * ((int64_t)jb.strips_x * jb.strips_y + jb.tail_bands);
+            grid = dim3((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock), 1);
+            if ((int64_t)grid.x <= (int64_t)resident_blocks<COLS, BETA, IO>() * wz_device_cus())
+                hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, true, true>), grid, dim3(kBlock), 0, st, jb, P, rows);
+            else
+                hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, false, true>), grid, dim3(kBlock), 0, st, jb, P,
+                                   rows);
+            return hipGetLastError();
+        }
+    }
+    const int64_t blocks = (int64_t)grid.x * grid.y;
+    if (blocks <= (int64_t)resident_blocks<COLS, BETA, IO>() * wz_device_cus())
+        hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, true>), grid, dim3(kBlock), 0, st, jb, P, rows);
+    else
+        hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, false>), grid, dim3(kBlock), 0, st, jb, P, rows);
+    return hipGetLastError();
+}
+
+// persistent launch: as many workgroups as the device holds, no more than there
+// are items for
+template <int COLS, int BETA, int IO>
+hipError_t launch_batched(const weno_batch_plan_t* plan, hipStream_t st)
+{
+    int64_t blocks = (int64_t)wz_device_cus() * resident_blocks<COLS, BETA, IO>();
+    const int64_t by_work = (plan->total_items + kWavesPerBlock - 1) / kWavesPerBlock;
+    if (blocks > by_work) blocks = by_work;
+    BatchTable* const tab = (BatchTable*)plan->d_workspace;
+    hipLaunchKernelGGL((zoom2x_batched_kernel<COLS, BETA, IO>), dim3((unsigned)blocks), dim3(kBlock), 0, st,
+                       (const BatchTable*)tab, &tab->counter[IO], plan->rows_per_strip);
+    return hipGetLastError();
+}
+
+template <int COLS, int IO>
+hipError_t single_beta(const FwdJob& jb, const FwdParams& P, int beta_mode, int rows, hipStream_t st)
+{
+    if (beta_mode == 2) return launch_single<COLS, 2, IO>(jb, P, rows, st);
+    if (beta_mode == 1) return launch_single<COLS, 1, IO>(jb, P, rows, st);
+    return launch_single<COLS, kBetaGeneral, IO>(jb, P, rows, st);
+}
+
+template <int COLS, int IO>
+hipError_t batched_beta(const weno_batch_plan_t* plan, hipStream_t st)
+{
+    if (plan->beta_mode == 2) return launch_batched<COLS, 2, IO>(plan, st);
+    if (plan->beta_mode == 1) return launch_batched<COLS, 1, IO>(plan, st);
+    return launch_batched<COLS, kBetaGeneral, IO>(plan, st);
+}
+
+hipError_t single(const FwdJob& jb, const FwdParams& P, int beta_mode, int cols, int rows, hipStream_t st)
+{
+    return cols == 1 ? single_beta<1, WENO_IO>(jb, P, beta_mode, rows, st)
+                     : single_beta<2, WENO_IO>(jb, P, beta_mode, rows, st);
+}
+
+hipError_t batched(const weno_batch_plan_t* plan, hipStream_t st)
+{
+    return plan->cols_per_lane == 1 ? batched_beta<1, WENO_IO>(plan, st) : batched_beta<2, WENO_IO>(plan, st);
+}
+
+}  // namespace
+
+template <>
+ZoomLauncher zoom_launcher<WENO_IO>()
+{
+    return {single, batched};
+}

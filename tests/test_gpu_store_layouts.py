@@ -74,3 +74,28 @@ def test_interleaved_automatic_shapes(gpu, shape):
     out, _ = _dest("hwc", n, c, 2 * h, 2 * w, torch.float32)
     gpu.zoom2x_(x.contiguous(memory_format=torch.channels_last), out)
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("beta", [2.0, 1.5])
+def test_batch_of_mixed_layouts(gpu, beta):
+    # one queue per layout and type: each image as alone, on every run of the plan
+    kinds = [("hwc", torch.uint8, torch.uint8), ("planar", torch.float32, torch.float32),
+             ("hwc", torch.uint8, torch.float32), ("planar", torch.uint8, torch.uint8),
+             ("spread", torch.float32, torch.float32), ("planar", torch.float32, torch.uint8),
+             ("hwc", torch.float32, torch.uint8), ("planar", torch.uint8, torch.float32)]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    xs, outs, refs = [], [], []
+    for i in range(3 * len(kinds)):
+        layout, src, dst = kinds[i % len(kinds)]
+        h, w = 9 + 13 * i, 200 - 7 * i
+        v = torch.rand((1, 3, h, w), generator=gen, device="cuda")
+        xs.append((255 * v).round().to(torch.uint8) if src == torch.uint8 else v)
+        outs.append(_dest(layout, 1, 3, 2 * h, 2 * w, dst)[0])
+        refs.append(gpu.zoom2x(xs[-1], beta=beta, out_dtype=dst))
+    plan = gpu.BatchedZoom(xs, outs, gpu.Params(beta=beta))
+    for _ in range(3):
+        for o in outs:
+            o.zero_()
+        plan.run()
+        assert all(torch.equal(o, r) for o, r in zip(outs, refs))
