@@ -174,13 +174,6 @@ int wz_beta_mode(float beta)
     return kBetaGeneral;
 }
 
-// Planes of one image interleaved in memory (channels closer together than
-// rows, as in HWC): the same strip of its planes touches the same lines.
-static bool planes_share_lines(int C, int64_t sc, int64_t sh)
-{
-    return C > 1 && std::llabs(sc) < std::llabs(sh);
-}
-
 // Fill a FwdJob for src -> dst (shapes already validated).
 // The readable source region of src for a boundary mode: src itself, or
 // (WENO_BOUNDARY_EXTERNAL) rows -4 .. h+4 and columns -4 .. w+4 around it.

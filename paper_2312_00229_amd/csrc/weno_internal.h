@@ -64,6 +64,13 @@ double wz_nbw(const weno_params_t* p);
 int wz_beta_mode(float beta);
 int wz_device_cus();
 
+// Planes of one image interleaved in memory (channels closer together than
+// rows, as in HWC): the same strip of its planes touches the same lines.
+inline bool planes_share_lines(int C, int64_t sc, int64_t sh)
+{
+    return C > 1 && sc < sh   /* strides are never negative */;
+}
+
 // Workgroups of a plane of `strips` strips: padded to a multiple of the XCD
 // count when the planes share lines (zoom2x_kernel), the padding exiting at
 // once.  The busiest XCD then holds planes x grid_x / 8 of them.

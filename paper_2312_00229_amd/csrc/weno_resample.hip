@@ -15,8 +15,9 @@
 //   SI_1    = b1^2 - 2 b1 b2 + (16/3) b2^2
 // Output sample j of an axis of n_out samples sits at x_j = j (n_in - 1)/(n_out - 1)
 // (end points aligned), computed in integers so that t is exact to FP32
-// rounding; samples on input nodes are copied.  The two passes (rows, then
-// columns) go through an FP32 intermediate in the caller's workspace.
+// rounding; samples on input nodes are copied.  One kernel resamples rows, then
+// columns, a wave at a time; only width ratios beyond ~16 take two passes
+// through an FP32 intermediate in the caller's workspace.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -41,30 +42,80 @@ namespace {
 // passes eps = 1: the weights are then C_s whatever the indicators).  A node
 // (t = 0, wmask = 0) gets omega_1 = 0 (the reciprocal is of a positive finite
 // number), so u = p_i = v_i exactly.
+// What the taps alone decide, whatever t: the weights' factors e0, e1 (beta = 2:
+// E_0^2 and E_1^2; other beta: e0 = (E_1/E_0)^beta).
+struct Interval {
+    float v0, v1, v2;        // v_i, v_{i+1}, v_{i+2}
+    float A1, A2, B1, B2;
+    float e0, e1;
+};
+
 template <int BETA>
-__device__ __forceinline__ float blend(float vm, float v0, float v1, float v2, float t, float s, float ht, float hs,
-                                       float k, float eps4, float beta, float wmask = 1.0f)
+__device__ __forceinline__ void interval_weights(Interval& I, float eps4, float beta)
 {
-    const float A1 = v1 - vm;
-    const float A2 = __builtin_fmaf(v0, -2.0f, v1 + vm);
-    const float B1 = v2 - v0;
-    const float B2 = __builtin_fmaf(v1, -2.0f, v2 + v0);
-    const float p0 = __builtin_fmaf(ht, __builtin_fmaf(t, A2, A1), v0);
-    const float p1 = __builtin_fmaf(hs, __builtin_fmaf(s, B2, B1), v1);
-    const float E0 = __builtin_fmaf(A2, __builtin_fmaf(A2, 16.0f / 3.0f, A1 + A1), __builtin_fmaf(A1, A1, eps4));
-    const float E1 = __builtin_fmaf(B2, __builtin_fmaf(B2, 16.0f / 3.0f, -(B1 + B1)), __builtin_fmaf(B1, B1, eps4));
+    const float E0 = __builtin_fmaf(I.A2, __builtin_fmaf(I.A2, 16.0f / 3.0f, I.A1 + I.A1),
+                                    __builtin_fmaf(I.A1, I.A1, eps4));
+    const float E1 = __builtin_fmaf(I.B2, __builtin_fmaf(I.B2, 16.0f / 3.0f, -(I.B1 + I.B1)),
+                                    __builtin_fmaf(I.B1, I.B1, eps4));
+    if constexpr (BETA == 2) {
+        I.e0 = E0 * E0;
+        I.e1 = E1 * E1;
+    } else {
+        I.e0 = __builtin_amdgcn_exp2f(beta * __builtin_amdgcn_logf(E1 * rcp(E0)));
+        I.e1 = 0.0f;
+    }
+}
+
+// (A1, A2) of the interval from its taps; (B1, B2) are those of the next one
+__device__ __forceinline__ void interval_left(Interval& I, float vm)
+{
+    I.A1 = I.v1 - vm;
+    I.A2 = __builtin_fmaf(I.v0, -2.0f, I.v1 + vm);
+}
+__device__ __forceinline__ void interval_right(Interval& I)
+{
+    I.B1 = I.v2 - I.v0;
+    I.B2 = __builtin_fmaf(I.v1, -2.0f, I.v2 + I.v0);
+}
+
+// position inside an interval, with the products of it that every sample needs
+struct InPos {
+    float t, s, ht, hs, k, wmask;
+};
+__device__ __forceinline__ InPos in_pos(float t, float k, bool node)
+{
+    const float s = t - 1.0f;
+    return {t, s, 0.5f * t, 0.5f * s, k, node ? 0.0f : 1.0f};
+}
+
+template <int BETA>
+__device__ __forceinline__ float interval_value(const Interval& I, const InPos& p)
+{
+    const float p0 = __builtin_fmaf(p.ht, __builtin_fmaf(p.t, I.A2, I.A1), I.v0);
+    const float p1 = __builtin_fmaf(p.hs, __builtin_fmaf(p.s, I.B2, I.B1), I.v1);
     float w1;
     if constexpr (BETA == 2) {
         // 1/(1 + k (E1/E0)^2) = E0^2 / (E0^2 + k E1^2): one reciprocal (the
         // denominator is at least (4 eps)^2; E^2 stays finite for samples
         // below ~4e9 in magnitude)
-        const float e0 = E0 * E0;
-        w1 = (e0 * wmask) * rcp(__builtin_fmaf(k, E1 * E1, e0));
+        w1 = (I.e0 * p.wmask) * rcp(__builtin_fmaf(p.k, I.e1, I.e0));
     } else {
-        const float g = __builtin_amdgcn_exp2f(beta * __builtin_amdgcn_logf(E1 * rcp(E0)));
-        w1 = rcp(__builtin_fmaf(k, g, 1.0f)) * wmask;
+        w1 = rcp(__builtin_fmaf(p.k, I.e0, 1.0f)) * p.wmask;
     }
     return __builtin_fmaf(w1, p1 - p0, p0);
+}
+
+template <int BETA>
+__device__ __forceinline__ float blend(float vm, float v0, float v1, float v2, const InPos& p, float eps4, float beta)
+{
+    Interval I;
+    I.v0 = v0;
+    I.v1 = v1;
+    I.v2 = v2;
+    interval_left(I, vm);
+    interval_right(I);
+    interval_weights<BETA>(I, eps4, beta);
+    return interval_value<BETA>(I, p);
 }
 
 // Source position of one output sample along an axis: the interval
@@ -77,10 +128,17 @@ struct SamplePos {
     int32_t node;
 };
 
-// Positions j (n_in - 1)/(n_out - 1) = i + t of an axis, one thread each,
-// worked out in integers so that nodes are exact; t and k are rounded once
-// from exact ratios.
-__device__ void sample_position(SamplePos* __restrict__ pos, int j, int n_in, int n_out)
+// Position j (n_in - 1)/(n_out - 1) = i + t of an axis, worked out in integers
+// so that nodes are exact; t and k = C_0/C_1 = (2 - t)/(t + 1) =
+// (2 den - rem)/(den + rem) are rounded once from exact ratios.  `small` (the
+// same for all samples of an axis): 32-bit products and float operands hold
+// every value exactly; a float division of exact operands rounds as the double
+// one rounded to float does.
+__device__ __forceinline__ bool small_axis(int n_in, int n_out)
+{
+    return (uint64_t)n_in * (uint64_t)n_out < (1ull << 32) && n_out < (1 << 22);
+}
+__device__ __forceinline__ SamplePos sample_position(int j, int n_in, int n_out, bool small)
 {
     SamplePos p;
     p.i = 0;
@@ -88,10 +146,18 @@ __device__ void sample_position(SamplePos* __restrict__ pos, int j, int n_in, in
     p.k = 2.0f;
     p.node = 1;
     if (n_out > 1 && n_in > 1) {
-        const uint64_t num = (uint64_t)j * (uint64_t)(n_in - 1);
-        const uint64_t den = (uint64_t)(n_out - 1);
-        int i = (int)(num / den);
-        const uint64_t rem = num - (uint64_t)i * den;
+        const uint32_t den = (uint32_t)(n_out - 1);
+        int i;
+        uint32_t rem;
+        if (small) {
+            const uint32_t num = (uint32_t)j * (uint32_t)(n_in - 1);
+            i = (int)(num / den);
+            rem = num - (uint32_t)i * den;
+        } else {
+            const uint64_t num = (uint64_t)j * (uint64_t)(n_in - 1);
+            i = (int)(num / den);
+            rem = (uint32_t)(num - (uint64_t)i * den);
+        }
         if (i > n_in - 2) {
             p.i = n_in - 1;          // the last node
         } else if (rem == 0) {
@@ -99,12 +165,16 @@ __device__ void sample_position(SamplePos* __restrict__ pos, int j, int n_in, in
         } else {
             p.i = i;
             p.node = 0;
-            p.t = (float)((double)rem / (double)den);
-            // C_0/C_1 = (2 - t)/(t + 1) = (2 den - rem)/(den + rem)
-            p.k = (float)((double)(2 * den - rem) / (double)(den + rem));
+            if (small) {
+                p.t = (float)rem / (float)den;
+                p.k = (float)(2 * den - rem) / (float)(den + rem);
+            } else {
+                p.t = (float)((double)rem / (double)den);
+                p.k = (float)((double)(2 * (uint64_t)den - rem) / (double)((uint64_t)den + rem));
+            }
         }
     }
-    pos[j] = p;
+    return p;
 }
 
 // both tables in one launch: rows first, then columns
@@ -112,8 +182,8 @@ __global__ __launch_bounds__(256) void positions_kernel(SamplePos* __restrict__ 
                                                         SamplePos* __restrict__ cols, int w_in, int w_out)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < h_out) sample_position(rows, j, h_in, h_out);
-    else if (j - h_out < w_out) sample_position(cols, j - h_out, w_in, w_out);
+    if (j < h_out) rows[j] = sample_position(j, h_in, h_out, small_axis(h_in, h_out));
+    else if (j - h_out < w_out) cols[j - h_out] = sample_position(j - h_out, w_in, w_out, small_axis(w_in, w_out));
 }
 
 // Work split of both passes: a wave owns kCpl columns per lane (64 apart, so
@@ -195,12 +265,12 @@ __global__ __launch_bounds__(256) void rows_pass_kernel(RowPassArgs a, const Sam
         T.k = p.k;
     };
     auto emit = [&](const Taps& T, int r) {
-        const float t = T.t, s = t - 1.0f, ht = 0.5f * t, hs = 0.5f * s;
+        const InPos p = in_pos(T.t, T.k, false);
         const uint32_t so = (uint32_t)r * a.t_h;
 #pragma unroll
         for (int j = 0; j < kCpl; ++j)
-            buf_st_f32(blend<BETA>((float)T.v[0][j], (float)T.v[1][j], (float)T.v[2][j], (float)T.v[3][j], t, s, ht,
-                                   hs, T.k, a.eps4, a.beta) *
+            buf_st_f32(blend<BETA>((float)T.v[0][j], (float)T.v[1][j], (float)T.v[2][j], (float)T.v[3][j], p, a.eps4,
+                                   a.beta) *
                            kScale,
                        dst, vout[j], so);
     };
@@ -244,19 +314,14 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(ColPassArgs a, const Sam
     const rsrc_t src = make_rsrc(a.tmp + (size_t)plane * a.t_plane, a.t_plane);
     const rsrc_t dst = make_rsrc(a.dst + n * a.d_n + ch * a.d_c, a.d_extent);
     uint32_t vtap[kCpl], vout[kCpl];
-    float t[kCpl], s[kCpl], ht[kCpl], hs[kCpl], k[kCpl], wmask[kCpl];
+    InPos at[kCpl];
 #pragma unroll
     for (int j = 0; j < kCpl; ++j) {
         const int c = chunk * (64 * kCpl) + lane + 64 * j;
         const SamplePos p = pos[min(c, a.out_w - 1)];
         vtap[j] = (uint32_t)p.i * 4u;
         vout[j] = c < a.out_w ? (uint32_t)c * a.d_w : kOob;
-        wmask[j] = p.node ? 0.0f : 1.0f;
-        t[j] = p.t;
-        s[j] = p.t - 1.0f;
-        ht[j] = 0.5f * t[j];
-        hs[j] = 0.5f * s[j];
-        k[j] = p.k;
+        at[j] = in_pos(p.t, p.k, p.node);
     }
     struct Taps {
         float v[4][kCpl];
@@ -272,8 +337,7 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(ColPassArgs a, const Sam
         const uint32_t so = (uint32_t)r * a.d_h;
 #pragma unroll
         for (int j = 0; j < kCpl; ++j) {
-            const float u = blend<BETA>(T.v[0][j], T.v[1][j], T.v[2][j], T.v[3][j], t[j], s[j], ht[j], hs[j], k[j],
-                                        a.eps4, a.beta, wmask[j]);
+            const float u = blend<BETA>(T.v[0][j], T.v[1][j], T.v[2][j], T.v[3][j], at[j], a.eps4, a.beta);
             if constexpr (OUT_U8) buf_st_u8(quant_u8(u * 255.0f), dst, vout[j], so);
             else buf_st_f32(u, dst, vout[j], so);
         }
@@ -291,8 +355,210 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(ColPassArgs a, const Sam
     if (r < r1) emit(A, r);
 }
 
-// Fused tensor resampler: a block of 256 threads owns a tile of `tw` output
-// columns and a run of output rows of one plane.  For each output row it
+// Fused tensor resampler: a wave owns a tile of `tw` output columns and a run
+// of output rows of one plane.  For each output row it first resamples the
+// four input rows of that row's interval at the input columns its columns'
+// intervals touch (columns xa .. xa + 64 M - 1, xa = i(c0) - 1, clamped), into
+// its LDS row, then resamples that row along the columns; the float
+// intermediate of the two-pass form never leaves the CU.  The arithmetic,
+// operands and their order are those of the two passes, so both forms give
+// the same bits.
+//
+// What bounds it is vector issue where it enlarges and memory where it
+// shrinks (3x4319x7679 -> 3240x5760: 146 us; 97 us with all reads and writes
+// hitting the caches, 120 with the writes alone doing so; 4.3 TB/s against the
+// 5.1 of a plain copy), so nothing may hold a wave up.  The LDS row is the
+// wave's own, and LDS serves a wave in order: there is no barrier.  The wave
+// walks the input intervals one by one with kAhead rows requested ahead; the
+// tap rows and the rows in flight are a ring of registers that turns by
+// renaming, eight intervals per trip.  What an interval's taps alone decide
+// (Interval) is worked out once for all its output rows, and not at all for
+// an interval without any.  Each lane works out the positions of its columns
+// and of one row of the run, which is read from that lane: no position tables,
+// no launch before this one (about 3 us).  A block is four waves on
+// neighbouring tiles.  Against a block kernel with a barrier per output row
+// and position tables: 1080p -> 1440p uint8 HWC 22.9 -> 19.7 us, float32
+// 3x2160x3840 -> 864x1536 24.8 -> 20.4, 3x200x300 -> 260x390 10.3 -> 7.4,
+// 3x720x1280 -> 2160x3840 35.2 -> 33.9.
+constexpr int kTileQ = 4;          // output columns per lane at most
+constexpr int kMaxRun = kWave;     // output rows of a wave at most: a lane holds a row's position
+constexpr int kAhead = 4;          // input rows in flight
+constexpr int kRing = 4 + kAhead;
+
+struct WaveArgs {
+    const uint8_t* src;
+    uint8_t* dst;
+    int64_t s_n, s_c, d_n, d_c;
+    uint32_t s_h, s_w, d_h, d_w;
+    uint32_t src_extent, d_extent;
+    int32_t C, planes, in_h, in_w, out_h, out_w;
+    int32_t tw, ctiles, run;          // tile width, tiles per row, rows per run
+    int32_t share;                    // planes interleaved in memory
+    int32_t reverse;                  // planes in reverse order
+    int32_t paced;                    // one round of waves
+    float eps4_in, eps4, beta;        // eps4_in in the input's value scale, eps4 on the float scale
+};
+
+// M: LDS slots per lane; Q: output columns per lane at most
+template <int BETA, int M, int Q, bool IN_U8, bool OUT_U8>
+__global__ __launch_bounds__(kBlock) void wave_resample_kernel(WaveArgs a)
+{
+    __shared__ float rows_lds[kWavesPerBlock][kWave * M];
+    const int lane = threadIdx.x & (kWave - 1);
+    // the block's place: as the doubling's (zoom2x_kernel), every XCD gets a
+    // contiguous range of blocks, and those of a tile's interleaved planes
+    // follow each other on one XCD
+    const int nb = gridDim.x, b = blockIdx.x;
+    const int xcd = b % kXcds, kb = b / kXcds;
+    int plane, blk;
+    if (a.share) {
+        const int per_xcd = nb / (kXcds * a.planes);
+        const int n = kb / (per_xcd * a.C), r = kb - n * per_xcd * a.C;
+        plane = n * a.C + r % a.C;
+        blk = xcd * per_xcd + r / a.C;
+    } else {
+        plane = a.reverse ? a.planes - 1 - blockIdx.y : blockIdx.y;
+        blk = xcd * (nb / kXcds) + min(xcd, nb % kXcds) + kb;
+    }
+    const int tile = __builtin_amdgcn_readfirstlane(blk * kWavesPerBlock + (threadIdx.x >> 6));
+    const int rr = tile / a.ctiles, ct = tile - rr * a.ctiles;
+    const int r0 = rr * a.run, r1 = min(r0 + a.run, a.out_h);
+    if (r0 >= a.out_h) return;   // whole wave; there is no barrier
+    const int n = plane / a.C, ch = plane - n * a.C;
+    const rsrc_t src = make_rsrc(a.src + n * a.s_n + ch * a.s_c, a.src_extent);
+    const rsrc_t dst = make_rsrc(a.dst + n * a.d_n + ch * a.d_c, a.d_extent);
+    const int c0 = ct * a.tw, c1 = min(c0 + a.tw, a.out_w);
+    const int live = c1 - c0;   // columns of the tile (uniform)
+    const bool small_w = small_axis(a.in_w, a.out_w);
+    // lane l holds the position of the run's row l
+    const SamplePos rp = sample_position(min(r0 + lane, a.out_h - 1), a.in_h, a.out_h, small_axis(a.in_h, a.out_h));
+    // column phase: per output column, the LDS index of its first tap and its weights
+    int lb[Q];
+    uint32_t vout[Q];
+    InPos cp[Q];
+    // the tile's span of input columns: its first column sits in lane 0, and
+    // lanes past its last repeat that
+    int xa = 0, xb = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        lb[q] = 0;
+        vout[q] = kOob;
+        cp[q] = {};
+        if (kWave * q >= live) break;
+        const int c = c0 + lane + kWave * q;
+        const SamplePos p = sample_position(min(c, c1 - 1), a.in_w, a.out_w, small_w);
+        if (q == 0) xa = __builtin_amdgcn_readfirstlane(p.i) - 1;
+        xb = __builtin_amdgcn_readlane(p.i, kWave - 1) + 2;
+        lb[q] = p.i - 1 - xa;
+        vout[q] = c < c1 ? (uint32_t)c * a.d_w : kOob;
+        cp[q] = in_pos(p.t, p.k, p.node);
+    }
+    // row phase: the input columns of this lane's LDS slots (slots past the
+    // span load nothing: their values are never read)
+    uint32_t vin[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int x = xa + lane + kWave * m;
+        vin[m] = x <= xb ? (uint32_t)min(max(x, 0), a.in_w - 1) * a.s_w : kOob;
+    }
+    constexpr float kScale = IN_U8 ? 1.0f / 255.0f : 1.0f;
+    auto position = [&](int r) {
+        SamplePos u;
+        u.i = __builtin_amdgcn_readlane(rp.i, r - r0);
+        u.node = __builtin_amdgcn_readlane(rp.node, r - r0);
+        u.t = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rp.t), r - r0));
+        u.k = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, rp.k), r - r0));
+        return u;
+    };
+    int r = r0;
+    SamplePos pc = position(r0);   // the next output row's
+    int x = pc.i;                  // the interval the walk is at
+    const int x_last = __builtin_amdgcn_readlane(rp.i, r1 - 1 - r0) + 2;   // the last input row the run reads
+    // Interval x reads ring rows x - 1 .. x + 2 (clamped to the image), slots
+    // k .. k + 3 of the ring at the trip's step k; slots k + 4 .. k + 7 are in
+    // flight.  Bytes become floats when their row becomes a tap.
+    float ring[kRing][M];
+    auto ld_row = [&](int slot, int row) {
+        const uint32_t so = (uint32_t)min(max(min(row, x_last), 0), a.in_h - 1) * a.s_h;
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            if constexpr (IN_U8)
+                ring[slot][m] = __builtin_bit_cast(
+                    float, (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(src, (int)vin[m], (int)so, 0));
+            else
+                ring[slot][m] = buf_ld_f32(src, vin[m], so);
+        }
+    };
+    auto arrive = [&](int slot) {
+        if constexpr (IN_U8) {
+#pragma unroll
+            for (int m = 0; m < M; ++m) ring[slot][m] = (float)__builtin_bit_cast(uint32_t, ring[slot][m]);
+        }
+    };
+    float* const buf = rows_lds[threadIdx.x >> 6];
+    const int q1 = r0 + (r1 - r0) / 4, q2 = r0 + (r1 - r0) / 2, q3 = r0 + 3 * (r1 - r0) / 4;
+    if (a.paced) __builtin_amdgcn_s_setprio(3);
+    auto emit = [&](const Interval (&I)[M]) {
+        // a node row (t = 0, omega_1 masked) is its own tap v0, exactly
+        const InPos p = in_pos(pc.t, pc.k, pc.node);
+#pragma unroll
+        for (int m = 0; m < M; ++m) buf[lane + kWave * m] = interval_value<BETA>(I[m], p) * kScale;
+        const uint32_t so = (uint32_t)r * a.d_h;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (kWave * q >= live) break;
+            const float* L = buf + lb[q];
+            const float u = blend<BETA>(L[0], L[1], L[2], L[3], cp[q], a.eps4, a.beta);
+            if constexpr (OUT_U8) buf_st_u8(quant_u8(u * 255.0f), dst, vout[q], so);
+            else buf_st_f32(u, dst, vout[q], so);
+        }
+        ++r;
+        if (r < r1) pc = position(r);
+        if (a.paced) {   // as the doubling's one-round launches (zoom_strip)
+            if (r == q1) __builtin_amdgcn_s_setprio(2);
+            else if (r == q2) __builtin_amdgcn_s_setprio(1);
+            else if (r == q3) __builtin_amdgcn_s_setprio(0);
+        }
+    };
+    auto step = [&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        constexpr int k1 = (k + 1) % kRing, k2 = (k + 2) % kRing, k3 = (k + 3) % kRing;
+        arrive(k3);
+        if (pc.i == x) {
+            Interval I[M];
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                I[m].v0 = ring[k1][m];
+                I[m].v1 = ring[k2][m];
+                I[m].v2 = ring[k3][m];
+                interval_left(I[m], ring[k][m]);
+                interval_right(I[m]);
+                interval_weights<BETA>(I[m], a.eps4_in, a.beta);
+            }
+            ld_row(k, x + 3 + kAhead);
+            do {
+                emit(I);
+            } while (r < r1 && pc.i == x);
+        } else {
+            ld_row(k, x + 3 + kAhead);
+        }
+        ++x;
+        return r < r1;
+    };
+#pragma unroll
+    for (int k = 0; k < kRing; ++k) ld_row(k, x - 1 + k);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) arrive(k);
+    while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{}) &&
+           step(std::integral_constant<int, 2>{}) && step(std::integral_constant<int, 3>{}) &&
+           step(std::integral_constant<int, 4>{}) && step(std::integral_constant<int, 5>{}) &&
+           step(std::integral_constant<int, 6>{}) && step(std::integral_constant<int, 7>{})) {
+    }
+}
+
+// Fused tensor resampler for width or height ratios above ~4 (below, the wave
+// kernel): a block of 256 threads owns a tile of `tw` output columns and a run
+// of output rows of one plane.  For each output row it
 // first resamples the four input rows of that row's interval at the input
 // columns its columns' intervals touch (columns xa .. xa + 256 M - 1, xa =
 // i(c0) - 1, clamped), into an LDS row, then resamples that row along the
@@ -304,7 +570,7 @@ constexpr int kFuseQ = 3;          // output columns per thread at most (tw <= 7
 constexpr int kFuseThreads = 256;  // threads per block (LDS slots per row: kFuseThreads M)
 constexpr int kFuseMaxTw = kFuseThreads * kFuseQ;
 
-struct FusedArgs {
+struct BlockArgs {
     const uint8_t* src;
     uint8_t* dst;
     int64_t s_n, s_c, d_n, d_c;
@@ -316,7 +582,7 @@ struct FusedArgs {
 };
 
 template <int BETA, int M, bool IN_U8, bool OUT_U8>
-__global__ __launch_bounds__(kFuseThreads) void fused_resample_kernel(FusedArgs a,
+__global__ __launch_bounds__(kFuseThreads) void block_resample_kernel(BlockArgs a,
                                                                       const SamplePos* __restrict__ prow,
                                                                       const SamplePos* __restrict__ pcol)
 {
@@ -342,7 +608,7 @@ __global__ __launch_bounds__(kFuseThreads) void fused_resample_kernel(FusedArgs 
     // column phase: per output column, the LDS index of its first tap and its weights
     int lb[kFuseQ];
     uint32_t vout[kFuseQ];
-    float t[kFuseQ], s[kFuseQ], ht[kFuseQ], hs[kFuseQ], k[kFuseQ], wmask[kFuseQ];
+    InPos cp[kFuseQ];
     int live = 0;   // bit q: the wave owns a column of slot q (uniform)
 #pragma unroll
     for (int q = 0; q < kFuseQ; ++q) {
@@ -351,12 +617,7 @@ __global__ __launch_bounds__(kFuseThreads) void fused_resample_kernel(FusedArgs 
         const SamplePos p = pcol[min(c, a.out_w - 1)];
         lb[q] = p.i - 1 - xa;
         vout[q] = c < c1 ? (uint32_t)c * a.d_w : kOob;
-        t[q] = p.t;
-        s[q] = p.t - 1.0f;
-        ht[q] = 0.5f * t[q];
-        hs[q] = 0.5f * s[q];
-        k[q] = p.k;
-        wmask[q] = p.node ? 0.0f : 1.0f;
+        cp[q] = in_pos(p.t, p.k, p.node);
     }
     live = __builtin_amdgcn_readfirstlane(live);
     constexpr float kScale = IN_U8 ? 1.0f / 255.0f : 1.0f;
@@ -420,13 +681,11 @@ __global__ __launch_bounds__(kFuseThreads) void fused_resample_kernel(FusedArgs 
     auto step = [&](int r, float* buf) {
         {
             // a node row (t = 0, omega_1 masked) is its own tap W[1], exactly
-            const float tt = pc.t, ss = tt - 1.0f, htt = 0.5f * tt, hss = 0.5f * ss;
-            const float wm = pc.node ? 0.0f : 1.0f;
+            const InPos p = in_pos(pc.t, pc.k, pc.node);
 #pragma unroll
             for (int m = 0; m < M; ++m)
                 buf[tid + kFuseThreads * m] = blend<BETA>((float)W[m][0], (float)W[m][1], (float)W[m][2],
-                                                          (float)W[m][3], tt, ss, htt, hss, pc.k, a.eps4_in, a.beta,
-                                                          wm) *
+                                                          (float)W[m][3], p, a.eps4_in, a.beta) *
                                               kScale;
         }
         __syncthreads();
@@ -438,7 +697,7 @@ __global__ __launch_bounds__(kFuseThreads) void fused_resample_kernel(FusedArgs 
         for (int q = 0; q < kFuseQ; ++q) {
             if (!((live >> q) & 1)) continue;
             const float* L = buf + lb[q];
-            const float u = blend<BETA>(L[0], L[1], L[2], L[3], t[q], s[q], ht[q], hs[q], k[q], a.eps4, a.beta, wmask[q]);
+            const float u = blend<BETA>(L[0], L[1], L[2], L[3], cp[q], a.eps4, a.beta);
             if constexpr (OUT_U8) buf_st_u8(quant_u8(u * 255.0f), dst, vout[q], so);
             else buf_st_f32(u, dst, vout[q], so);
         }
@@ -547,20 +806,147 @@ int launch_cols_pass(const uint8_t* tmp, uint32_t t_h, const weno_tensor_t* dst,
     return e == hipSuccess ? WENO_OK : wz_hip_error(e, "cols_pass_kernel launch");
 }
 
-// Launch shape of the fused resampler along a row of n_in -> n_out samples:
+// Launch shape of the wave kernel along a row of n_in -> n_out samples: M LDS
+// slots per lane and a tile width tw <= 64 Q whose span fits the 64 M slots,
+// ceil((tw - 1)(n_in - 1)/(n_out - 1)) + 4 <= 64 M, with the row's tiles
+// balanced.  Slots and columns both cost a wave-wide evaluation per row,
+// whether all lanes need it or not, so the pair with the fewest per row is
+// taken.  m = 0: no tile of 64 columns fits 256 slots (width ratios above ~4).
+struct WaveShape {
+    int m, tw, ctiles;
+};
+
+WaveShape wave_shape(int n_in, int n_out)
+{
+    const int64_t num = n_in > 1 ? n_in - 1 : 0, den = n_out > 1 ? n_out - 1 : 1;
+    const int64_t min_tw = n_out < kWave ? n_out : kWave;
+    WaveShape best = {0, 0, 0};
+    int64_t best_cost = 0;
+    for (int m = 1; m <= 4; ++m) {
+        int64_t twmax = num == 0 ? kWave * kTileQ : ((int64_t)kWave * m - 4) * den / num + 1;
+        if (twmax < min_tw) continue;
+        if (twmax > kWave * kTileQ) twmax = kWave * kTileQ;
+        for (int64_t q = 1; q <= kTileQ; ++q) {
+            const int64_t tw = twmax < kWave * q ? twmax : kWave * q;
+            const int64_t tiles = (n_out + tw - 1) / tw;
+            const int64_t cost = tiles * (m + q);
+            if (best.m == 0 || cost < best_cost) {
+                best = {m, (int)((n_out + tiles - 1) / tiles), (int)tiles};
+                best_cost = cost;
+            }
+        }
+    }
+    return best;
+}
+
+// The wave kernel walks every input row between a run's first and last, so it
+// serves height ratios up to 4, where output rows read them all anyway.
+bool wave_rows(int n_in, int n_out) { return n_in <= 4 * (int64_t)n_out; }
+
+// Rows per run of the wave kernel.  per_simd: the rows of tiles each SIMD gets.
+// A small launch is one round of four waves per SIMD, paced: starting a wave
+// costs about four rows, and a second round would pay it again (1080p ->
+// 1440p uint8 HWC: two, three or four waves per SIMD 25.4 / 22.4 / 21.7 us,
+// two rounds of 5-row runs 26.6).  A large one takes several rounds of 12 to
+// 18 rows, which keep the rows read and written by neighbouring waves close in
+// time (3x4319x7679 -> 3240x5760: runs of 18 / 37 / 64 rows 146 / 151 / 166 us).
+struct WaveRun {
+    int rows;
+    bool paced;
+};
+
+WaveRun wave_run(int out_h, int ctiles, int64_t planes)
+{
+    const int64_t simds = (int64_t)wz_device_cus() * kWavesPerBlock;
+    const int64_t per_simd = (out_h * (int64_t)ctiles * planes + simds - 1) / simds;
+    if (per_simd <= 64) {
+        const int64_t run = (per_simd + 3) / 4;
+        return {(int)(run < 4 ? 4 : run), true};
+    }
+    const int64_t run = per_simd / 8;
+    return {(int)(run < 12 ? 12 : (run > 18 ? 18 : run)), false};
+}
+
+template <int BETA, int M>
+void launch_wave_typed(const WaveArgs& a, bool in_u8, bool out_u8, dim3 grid, hipStream_t st)
+{
+    if (in_u8 && out_u8)
+        hipLaunchKernelGGL((wave_resample_kernel<BETA, M, kTileQ, true, true>), grid, dim3(kBlock), 0, st, a);
+    else if (in_u8)
+        hipLaunchKernelGGL((wave_resample_kernel<BETA, M, kTileQ, true, false>), grid, dim3(kBlock), 0, st, a);
+    else if (out_u8)
+        hipLaunchKernelGGL((wave_resample_kernel<BETA, M, kTileQ, false, true>), grid, dim3(kBlock), 0, st, a);
+    else
+        hipLaunchKernelGGL((wave_resample_kernel<BETA, M, kTileQ, false, false>), grid, dim3(kBlock), 0, st, a);
+}
+
+template <int BETA>
+void launch_wave_beta(const WaveArgs& a, int m, bool in_u8, bool out_u8, dim3 grid, hipStream_t st)
+{
+    switch (m) {
+    case 1: launch_wave_typed<BETA, 1>(a, in_u8, out_u8, grid, st); break;
+    case 2: launch_wave_typed<BETA, 2>(a, in_u8, out_u8, grid, st); break;
+    case 3: launch_wave_typed<BETA, 3>(a, in_u8, out_u8, grid, st); break;
+    default: launch_wave_typed<BETA, 4>(a, in_u8, out_u8, grid, st); break;
+    }
+}
+
+int launch_wave(const weno_tensor_t* src, const weno_tensor_t* dst, const WaveShape& fs, const weno_params_t* p,
+                 double h, bool reverse, hipStream_t st)
+{
+    WaveArgs a;
+    const int64_t ei = wz_esize(src->dtype), eo = wz_esize(dst->dtype);
+    const bool in_u8 = src->dtype == WENO_U8, out_u8 = dst->dtype == WENO_U8;
+    a.src = (const uint8_t*)src->data;
+    a.dst = (uint8_t*)dst->data;
+    a.s_n = src->sn * ei;
+    a.s_c = src->sc * ei;
+    a.d_n = dst->sn * eo;
+    a.d_c = dst->sc * eo;
+    a.s_h = (uint32_t)(src->sh * ei);
+    a.s_w = (uint32_t)(src->sw * ei);
+    a.d_h = (uint32_t)(dst->sh * eo);
+    a.d_w = (uint32_t)(dst->sw * eo);
+    a.src_extent = (uint32_t)wz_plane_extent(src);
+    a.d_extent = (uint32_t)wz_plane_extent(dst);
+    a.C = src->c;
+    a.in_h = src->h;
+    a.in_w = src->w;
+    a.out_h = dst->h;
+    a.out_w = dst->w;
+    a.tw = fs.tw;
+    a.ctiles = fs.ctiles;
+    a.planes = src->n * src->c;
+    a.share = planes_share_lines(src->c, src->sc, src->sh) || planes_share_lines(dst->c, dst->sc, dst->sh);
+    const WaveRun wr = wave_run(dst->h, fs.ctiles, a.planes);
+    a.run = wr.rows;
+    a.paced = wr.paced;
+    a.reverse = reverse;
+    a.eps4_in = eps4_of(p, h, in_u8);
+    a.eps4 = eps4_of(p, h, false);
+    a.beta = p->beta;
+    const int64_t waves = (int64_t)((dst->h + a.run - 1) / a.run) * fs.ctiles;
+    int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
+    if (a.share) blocks = (blocks + kXcds - 1) / kXcds * kXcds * a.planes;
+    const dim3 grid((unsigned)blocks, a.share ? 1u : (unsigned)a.planes);
+    if (p->beta == 2.0f) launch_wave_beta<2>(a, fs.m, in_u8, out_u8, grid, st);
+    else launch_wave_beta<kBetaGeneral>(a, fs.m, in_u8, out_u8, grid, st);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? WENO_OK : wz_hip_error(e, "wave_resample_kernel launch");
+}
+
+// Launch shape of the block kernel along a row of n_in -> n_out samples:
 // 256 M LDS slots per row and a tile width tw <= 768 whose span fits them,
 // ceil((tw - 1)(n_in - 1)/(n_out - 1)) + 4 <= 256 M, with the row's tiles
 // balanced.  M = 2 is taken wherever it allows tiles of 64 columns (width
-// ratios up to ~7.9): it measured fastest from upsampling by 1.5 to
-// downsampling by 1.9, against M = 1 (more tiles, each paying a barrier and
-// its pipeline fill per row) and M = 4 (twice the tap registers).  Larger
-// ratios take M = 3 or 4; beyond ~16, ok = false and the two passes run.
-struct FusedShape {
+// ratios up to ~7.9).  Larger ratios take M = 3 or 4; beyond ~16, ok = false
+// and the two passes run.
+struct BlockShape {
     bool ok;
     int m, tw, ctiles;
 };
 
-FusedShape fused_shape(int n_in, int n_out)
+BlockShape block_shape(int n_in, int n_out)
 {
     const int64_t num = n_in > 1 ? n_in - 1 : 0, den = n_out > 1 ? n_out - 1 : 1;
     const int64_t min_tw = n_out < 64 ? n_out : 64;
@@ -574,9 +960,9 @@ FusedShape fused_shape(int n_in, int n_out)
     return {false, 0, 0, 0};
 }
 
-// rows per run of the fused resampler: 8 for small launches, up to 32 once
+// rows per run of the block kernel: 8 for small launches, up to 32 once
 // there are more than 16 runs' worth of tile rows per compute unit
-int fused_run(int out_h, int ctiles, int64_t planes)
+int block_run(int out_h, int ctiles, int64_t planes)
 {
     const int64_t tile_rows = (int64_t)out_h * ctiles * planes;
     int64_t run = tile_rows / (256 * 16);
@@ -586,34 +972,34 @@ int fused_run(int out_h, int ctiles, int64_t planes)
 }
 
 template <int BETA, int M>
-void launch_fused_typed(const FusedArgs& a, bool in_u8, bool out_u8, dim3 grid, const SamplePos* prow,
+void launch_block_typed(const BlockArgs& a, bool in_u8, bool out_u8, dim3 grid, const SamplePos* prow,
                         const SamplePos* pcol, hipStream_t st)
 {
     if (in_u8 && out_u8)
-        hipLaunchKernelGGL((fused_resample_kernel<BETA, M, true, true>), grid, dim3(kFuseThreads), 0, st, a, prow, pcol);
+        hipLaunchKernelGGL((block_resample_kernel<BETA, M, true, true>), grid, dim3(kFuseThreads), 0, st, a, prow, pcol);
     else if (in_u8)
-        hipLaunchKernelGGL((fused_resample_kernel<BETA, M, true, false>), grid, dim3(kFuseThreads), 0, st, a, prow, pcol);
+        hipLaunchKernelGGL((block_resample_kernel<BETA, M, true, false>), grid, dim3(kFuseThreads), 0, st, a, prow, pcol);
     else if (out_u8)
-        hipLaunchKernelGGL((fused_resample_kernel<BETA, M, false, true>), grid, dim3(kFuseThreads), 0, st, a, prow, pcol);
+        hipLaunchKernelGGL((block_resample_kernel<BETA, M, false, true>), grid, dim3(kFuseThreads), 0, st, a, prow, pcol);
     else
-        hipLaunchKernelGGL((fused_resample_kernel<BETA, M, false, false>), grid, dim3(kFuseThreads), 0, st, a, prow, pcol);
+        hipLaunchKernelGGL((block_resample_kernel<BETA, M, false, false>), grid, dim3(kFuseThreads), 0, st, a, prow, pcol);
 }
 
 template <int BETA>
-void launch_fused_beta(const FusedArgs& a, int m, bool in_u8, bool out_u8, dim3 grid, const SamplePos* prow,
+void launch_block_beta(const BlockArgs& a, int m, bool in_u8, bool out_u8, dim3 grid, const SamplePos* prow,
                        const SamplePos* pcol, hipStream_t st)
 {
     switch (m) {
-    case 2: launch_fused_typed<BETA, 2>(a, in_u8, out_u8, grid, prow, pcol, st); break;
-    case 3: launch_fused_typed<BETA, 3>(a, in_u8, out_u8, grid, prow, pcol, st); break;
-    default: launch_fused_typed<BETA, 4>(a, in_u8, out_u8, grid, prow, pcol, st); break;
+    case 2: launch_block_typed<BETA, 2>(a, in_u8, out_u8, grid, prow, pcol, st); break;
+    case 3: launch_block_typed<BETA, 3>(a, in_u8, out_u8, grid, prow, pcol, st); break;
+    default: launch_block_typed<BETA, 4>(a, in_u8, out_u8, grid, prow, pcol, st); break;
     }
 }
 
-int launch_fused(const weno_tensor_t* src, const weno_tensor_t* dst, const FusedShape& fs, const weno_params_t* p,
+int launch_block(const weno_tensor_t* src, const weno_tensor_t* dst, const BlockShape& fs, const weno_params_t* p,
                  double h, const SamplePos* prow, const SamplePos* pcol, hipStream_t st)
 {
-    FusedArgs a;
+    BlockArgs a;
     const int64_t ei = wz_esize(src->dtype), eo = wz_esize(dst->dtype);
     const bool in_u8 = src->dtype == WENO_U8, out_u8 = dst->dtype == WENO_U8;
     a.src = (const uint8_t*)src->data;
@@ -636,16 +1022,16 @@ int launch_fused(const weno_tensor_t* src, const weno_tensor_t* dst, const Fused
     a.tw = fs.tw;
     a.ctiles = fs.ctiles;
     const int64_t planes = (int64_t)src->n * src->c;
-    a.run = fused_run(dst->h, fs.ctiles, planes);
+    a.run = block_run(dst->h, fs.ctiles, planes);
     a.eps4_in = eps4_of(p, h, in_u8);
     a.eps4 = eps4_of(p, h, false);
     a.beta = p->beta;
     const int64_t runs = (dst->h + a.run - 1) / a.run;
     const dim3 grid((unsigned)(runs * fs.ctiles), (unsigned)planes);
-    if (p->beta == 2.0f) launch_fused_beta<2>(a, fs.m, in_u8, out_u8, grid, prow, pcol, st);
-    else launch_fused_beta<kBetaGeneral>(a, fs.m, in_u8, out_u8, grid, prow, pcol, st);
+    if (p->beta == 2.0f) launch_block_beta<2>(a, fs.m, in_u8, out_u8, grid, prow, pcol, st);
+    else launch_block_beta<kBetaGeneral>(a, fs.m, in_u8, out_u8, grid, prow, pcol, st);
     const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? WENO_OK : wz_hip_error(e, "fused_resample_kernel launch");
+    return e == hipSuccess ? WENO_OK : wz_hip_error(e, "block_resample_kernel launch");
 }
 
 // row pitch (floats) of workspace planes: a multiple of 4, so that rows are
@@ -698,23 +1084,27 @@ int check_resample_pair(const weno_tensor_t* src, const weno_tensor_t* dst)
 static size_t resample_bytes(const weno_tensor_t* src, const weno_tensor_t* dst, int64_t in_w)
 {
     const size_t tabs = positions_bytes(dst->h) + positions_bytes(dst->w);
-    if (fused_shape((int)in_w, dst->w).ok) return tabs;
+    if (block_shape((int)in_w, dst->w).ok) return tabs;
     return tabs + planes_bytes((int64_t)src->n * src->c, dst->h, in_w + kPadCols);
 }
 
-// src (any dtype, in_h x in_w) resampled into dst: the fused kernel, or the
-// row pass then the column pass
+// src (any dtype, in_h x in_w) resampled into dst: a fused kernel, or the
+// row pass then the column pass.  reverse: src was just written plane by plane;
+// read the last planes first, while the memory-side cache holds them
+// (zoom_to 3x1080x1920 -> 3240x5760: 337 -> 332 us).
 static int run_resample(const weno_tensor_t* src, const weno_tensor_t* dst, const weno_params_t* p, double h,
-                        uint8_t* ws, hipStream_t st)
+                        uint8_t* ws, bool reverse, hipStream_t st)
 {
     SamplePos* rows = (SamplePos*)ws;
     SamplePos* cols = (SamplePos*)(ws + positions_bytes(dst->h));
     uint8_t* tmp = ws + positions_bytes(dst->h) + positions_bytes(dst->w);
-    const FusedShape fs = fused_shape(src->w, dst->w);
-    if (fs.ok) {
+    const WaveShape wave = wave_shape(src->w, dst->w);
+    if (wave.m > 0 && wave_rows(src->h, dst->h)) return launch_wave(src, dst, wave, p, h, reverse, st);
+    const BlockShape block = block_shape(src->w, dst->w);
+    if (block.ok) {
         int rc = launch_positions(rows, src->h, dst->h, cols, src->w, dst->w, st);
         if (rc) return rc;
-        return launch_fused(src, dst, fs, p, h, rows, cols, st);
+        return launch_block(src, dst, block, p, h, rows, cols, st);
     }
     const int64_t pitch = f32_pitch((int64_t)src->w + kPadCols);
     if ((int64_t)dst->h * pitch * 4 >= (1ll << 31)) return WENO_EINVAL;   // 32-bit plane offsets
@@ -743,7 +1133,7 @@ extern "C" int weno_resample(const weno_tensor_t* src, const weno_tensor_t* dst,
     if (p->boundary != WENO_BOUNDARY_CLAMP) return WENO_EINVAL;   // samples beyond the ends are clamped
     if (!d_workspace || (uintptr_t)d_workspace % 256 != 0) return WENO_EINVAL;   // tables and planes are aligned
     if (ws_bytes < weno_resample_workspace(src, dst)) return WENO_ENOSPC;
-    return run_resample(src, dst, p, p->h, (uint8_t*)d_workspace, (hipStream_t)hip_stream);
+    return run_resample(src, dst, p, p->h, (uint8_t*)d_workspace, false, (hipStream_t)hip_stream);
 }
 
 extern "C" size_t weno_zoom_to_workspace(const weno_tensor_t* src, const weno_tensor_t* dst)
@@ -802,5 +1192,5 @@ extern "C" int weno_zoom_to(const weno_tensor_t* src, const weno_tensor_t* dst, 
     }
     weno_params_t rp = *p;
     rp.h = (float)(p->h * std::ldexp(1.0, -k));
-    return run_resample(&cur, dst, &rp, rp.h, ws + off, st);
+    return run_resample(&cur, dst, &rp, rp.h, ws + off, k > 0, st);
 }
