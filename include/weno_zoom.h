@@ -116,17 +116,18 @@ int weno_zoom2x(const weno_tensor_t* src, const weno_tensor_t* dst, const weno_p
                 void* hip_stream);
 
 /*
- * Many independent images of uneven sizes in ONE persistent launch: the
- * workgroups pull row strips of all images from a shared work queue (images
- * ordered largest first).  The outputs are bit-identical to weno_zoom2x
+ * Many independent images of uneven sizes in ONE persistent launch (one per
+ * combination of types and destination layout among them): a workgroup per
+ * compute unit, whose waves share out every grid-th row strip of the images
+ * (ordered largest first).  The outputs are bit-identical to weno_zoom2x
  * called per image with the same launch configuration.
  *
  * Two steps, so that the launch itself can be captured into a hipGraph:
  *   weno_zoom2x_batched_plan  validates every pair, writes the image table
  *       into the caller's DEVICE workspace (one host-to-device copy on the
  *       stream, after which the call waits for the stream) and fills `plan`;
- *   weno_zoom2x_batched_run   enqueues a one-thread reset of the queue head
- *       and the persistent kernel; it copies nothing and allocates nothing.
+ *   weno_zoom2x_batched_run   enqueues the persistent kernel; it copies
+ *       nothing, allocates nothing and writes nothing but the outputs.
  * weno_zoom2x_batched does both.
  *   srcs[i], dsts[i]: HOST arrays of `count` descriptors (device data), each
  *                     pair obeying the rules of weno_zoom2x; no output may
@@ -139,12 +140,12 @@ int weno_zoom2x(const weno_tensor_t* src, const weno_tensor_t* dst, const weno_p
 typedef struct {
     void* d_workspace;
     size_t ws_bytes;
-    int64_t total_items;     /* queue length (row strips of all planes) */
+    int64_t total_items;     /* row strips of all planes */
     int32_t count;
     int32_t rows_per_strip;  /* launch configuration captured at plan time */
     int32_t cols_per_lane;
     int32_t beta_mode;
-    int64_t reserved;
+    int64_t reserved;        /* set by the plan */
 } weno_batch_plan_t;
 
 size_t weno_zoom2x_batched_workspace(int32_t count);
@@ -158,7 +159,7 @@ int weno_zoom2x_batched(const weno_tensor_t* srcs, const weno_tensor_t* dsts, in
 /*
  * For callers that cannot allocate device memory (tight serving loops,
  * harnesses that forbid hipMalloc): weno_zoom2x_batched without a caller
- * workspace.  The image table and the queue head live in a fixed device
+ * workspace.  The image table lives in a fixed device
  * array inside the library, one per GPU, kept until the process ends
  * (about 700 KB).  The call allocates nothing; like weno_zoom2x_batched it
  * copies the table to the device and waits for the stream once before the

@@ -20,15 +20,6 @@
 
 using namespace wz;
 
-namespace {
-
-__global__ void reset_counter_kernel(BatchTable* tab)
-{
-    if (threadIdx.x < kIoModes) tab->counter[threadIdx.x] = 0ull;
-}
-
-}  // namespace
-
 // --------------------------------------------------------------------------
 // status / configuration
 // --------------------------------------------------------------------------
@@ -214,6 +205,7 @@ FwdJob wz_make_job(const weno_tensor_t* src, const weno_tensor_t* dst, int cols,
     jb.in_u8 = src->dtype == WENO_U8;
     jb.out_u8 = dst->dtype == WENO_U8;
     const int own = cols == 1 ? strip_own<1>() : strip_own<2>();
+    jb.rows = rows_per_strip;
     jb.strips_x = (src->w + own - 1) / own;
     jb.strips_y = (src->h + rows_per_strip - 1) / rows_per_strip;
     jb.tail_rows = 0;
@@ -488,6 +480,61 @@ static int batched_check(const weno_tensor_t* srcs, const weno_tensor_t* dsts, i
     return WENO_OK;
 }
 
+// Strip shape of a batch from the cost model of a single launch
+// (iteration_cost): a compute unit's waves share its strips out one by one, so
+// it takes the rounds of its busiest wave, about 0.4 of a round more than the
+// mean, at the rate of the waves that share a SIMD.  Two-column strips of bytes
+// cost more per iteration than the model's float rows (x 1.17).  Interleaved
+// float rows take short one-column strips: the planes of a strip drift apart
+// as they go down, and with them the parts of the lines that an L2 should put
+// together (256 float32 HWC images of 64 to 512 squared: 16 rows 566 us, 64
+// rows 720, two columns 633 and 796).  On six batches of 8 to 512 images, all
+// types, the pick is within 7 % of the best of 24 shapes (24 uint8 HWC images
+// of 85 to 415 squared 40-45 us, 512 of 32 to 1024 squared 2353; 32-row
+// two-column strips, the choice before, 49 and 2424).
+static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts, int32_t count, int* rows, int* cols)
+{
+    const int64_t cus = wz_device_cus();
+    bool bytes = false, spread = false;
+    int64_t together = 1;   // planes of a strip taken together
+    for (int i = 0; i < count; ++i) {
+        const bool share = planes_share_lines(srcs[i].c, srcs[i].sc, srcs[i].sh) ||
+                           planes_share_lines(dsts[i].c, dsts[i].sc, dsts[i].sh);
+        bytes = bytes || dsts[i].dtype == WENO_U8;
+        spread = spread || (dsts[i].dtype == WENO_F32 && share);
+        if (share) together = std::max<int64_t>(together, srcs[i].c);
+    }
+    double best = 0.0;
+    for (int c = 2; c >= 1; --c) {
+        if (spread && c == 2) continue;
+        const int own = c == 1 ? strip_own<1>() : strip_own<2>();
+        const int64_t resident = c == 1 ? 4 : 3;   // waves per SIMD (zoom2x_batched_kernel)
+        for (int r : {8, 16, 24, 32, 48, 64, 96}) {
+            if (spread && r > 16) break;
+            int64_t strips = 0, iterations = 0;
+            int longest = 0;
+            for (int i = 0; i < count; ++i) {
+                const int64_t walks = (int64_t)srcs[i].n * srcs[i].c * ((srcs[i].w + own - 1) / own);
+                const int64_t bands = (srcs[i].h + r - 1) / r;
+                strips += walks * bands;
+                iterations += walks * (srcs[i].h + kStartCost * bands);
+                longest = std::max(longest, (int)((srcs[i].h + bands - 1) / bands));
+            }
+            const int64_t per_cu = ((strips + together - 1) / together + cus - 1) / cus * together;
+            const int64_t m = std::min(resident, (per_cu + 3) / 4);   // waves per SIMD
+            const double rounds = (double)per_cu / (double)std::min(per_cu, 4 * resident);
+            double each = longest + kStartCost;
+            if (rounds > 1.0) each = std::max(each, (rounds + 0.4) * (double)iterations / (double)strips);
+            const double cost = (double)m * each * iteration_cost(c, m) * (bytes && c == 2 ? 1.17 : 1.0);
+            if (best == 0.0 || cost < best) {
+                best = cost;
+                *rows = r;
+                *cols = c;
+            }
+        }
+    }
+}
+
 extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_tensor_t* dsts, int32_t count,
                                         const weno_params_t* p, void* d_workspace, size_t ws_bytes,
                                         void* hip_stream, weno_batch_plan_t* plan)
@@ -500,15 +547,14 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
     rc = batched_check(srcs, dsts, count, p);
     if (rc) return rc;
     int rows = g_rows_per_strip.load(), cols = g_cols_per_lane.load();
-    if (rows == 0 || cols == 0) {  // the queue balances the load: moderate strips, two columns per lane
-        rows = 32;
-        cols = 2;
-    }
-    // by I/O mode (each has a queue of its own), then largest images first
+    if (rows == 0 || cols == 0) batched_config(srcs, dsts, count, &rows, &cols);
+    // by I/O mode (each has a launch of its own), then largest images first
     std::vector<FwdJob> made(count);
     std::vector<int> order(count);
     for (int i = 0; i < count; ++i) {
-        made[i] = wz_make_job(&srcs[i], &dsts[i], cols, rows, p->boundary, 0);
+        // bands of nearly equal height, `rows` at most
+        const int bands = (srcs[i].h + rows - 1) / rows;
+        made[i] = wz_make_job(&srcs[i], &dsts[i], cols, (srcs[i].h + bands - 1) / bands, p->boundary, 0);
         order[i] = i;
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
@@ -521,20 +567,24 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
     FwdJob* jobs = (FwdJob*)(host.data() + batch_jobs_offset());
     int64_t* prefix = (int64_t*)(host.data() + batch_prefix_offset(count));
     FwdParams* prm = (FwdParams*)(host.data() + batch_params_offset(count));
-    int64_t total = 0, modes = 0;
-    int io = 0;   // queues [0, io] have their first item
+    int64_t total = 0, modes = 0, items = 0;
+    int io = 0;   // modes [0, io] have their first unit
     for (int k = 0; k < count; ++k) {
         jobs[k] = made[order[k]];
         while (io < jobs[k].io) tab->first[++io] = total;
         modes |= 1ll << io;
         prm[k] = wz_fwd_params(p, jobs[k].in_u8, jobs[k].out_u8);
         prefix[k] = total;
-        total += (int64_t)jobs[k].planes * jobs[k].strips_x * jobs[k].strips_y;
+        const int64_t strips = (int64_t)jobs[k].planes * jobs[k].strips_x * jobs[k].strips_y;
+        const int together = wz_unit_planes(jobs[k]);
+        tab->slots[io] = std::max(tab->slots[io], together);
+        total += strips / together;
+        items += strips;
     }
     prefix[count] = total;
     while (io < kIoModes) tab->first[++io] = total;
     tab->count = count;
-    tab->total_items = total;
+    tab->total_items = items;
     tab->params_offset = batch_params_offset(count);
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e = hipMemcpyAsync(d_workspace, host.data(), host.size(), hipMemcpyHostToDevice, st);
@@ -543,7 +593,7 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
     if (e != hipSuccess) return wz_hip_error(e, "batch table copy");
     plan->d_workspace = d_workspace;
     plan->ws_bytes = ws_bytes;
-    plan->total_items = total;
+    plan->total_items = items;
     plan->count = count;
     plan->rows_per_strip = rows;
     plan->cols_per_lane = cols;
@@ -557,13 +607,10 @@ extern "C" int weno_zoom2x_batched_run(const weno_batch_plan_t* plan, void* hip_
     if (!plan || !plan->d_workspace || plan->count < 1 || plan->total_items < 1) return WENO_EINVAL;
     if (plan->cols_per_lane != 1 && plan->cols_per_lane != 2) return WENO_EINVAL;
     hipStream_t st = (hipStream_t)hip_stream;
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, (BatchTable*)plan->d_workspace);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return wz_hip_error(e, "reset_counter_kernel launch");
     // one launch per I/O mode among the images, nearly always one in all
     for (int io = 0; io < kIoModes; ++io) {
         if (!((plan->reserved >> io) & 1)) continue;
-        e = kZoomLaunchers[io].batched(plan, st);
+        const hipError_t e = kZoomLaunchers[io].batched(plan, st);
         if (e != hipSuccess) return wz_hip_error(e, "zoom2x_batched_kernel launch");
     }
     return WENO_OK;
@@ -581,7 +628,7 @@ extern "C" int weno_zoom2x_batched(const weno_tensor_t* srcs, const weno_tensor_
 // --------------------------------------------------------------------------
 // batched, without a caller workspace
 // --------------------------------------------------------------------------
-// The image table and queue head of weno_zoom2x_batched_noalloc live in this
+// The image table of weno_zoom2x_batched_noalloc lives in this
 // file-scope device array (one copy per GPU, alive until the process ends).
 // In host code its name is only a stand-in for the symbol: the device
 // address comes from hipGetSymbolAddress, once per device, and only that
@@ -621,8 +668,7 @@ extern "C" int weno_zoom2x_batched_noalloc(const weno_tensor_t* srcs, const weno
     rc = noalloc_scratch(&ws);
     if (rc) return rc;
     // the plan validates everything before it writes the table into the
-    // scratch (one host-to-device copy, then a wait on the stream); the run
-    // clears the queue head with a kernel before the persistent launch
+    // scratch (one host-to-device copy, then a wait on the stream)
     weno_batch_plan_t plan;
     rc = weno_zoom2x_batched_plan(srcs, dsts, count, p, ws, kNoAllocScratchBytes, hip_stream, &plan);
     if (rc) return rc;

@@ -99,6 +99,7 @@ struct FwdJob {
     int64_t d_n, d_c, d_h, d_w;       // byte strides of the destination
     int32_t in_u8, out_u8;            // element types (host)
     int32_t strips_x, strips_y;       // strips per plane (two-column strips only when tail_rows > 0)
+    int32_t rows;                     // strip height (the last band may be shorter)
     // tail_rows > 0: the columns left of the last two-column strip are
     // walked by one-column strips of tail_rows rows, tail_bands of them per
     // plane (single-image planar launches; zoom2x_kernel)

@@ -12,12 +12,13 @@
 // workspace by weno_zoom2x_batched_plan:
 //   [0, 256)                 BatchTable header
 //   [256, ...)               FwdJob jobs[count]       (by I/O mode, then largest image first)
-//   then                     int64_t prefix[count+1]  (first queue item of each image)
+//   then                     int64_t prefix[count+1]  (first unit of each image: a strip of one plane,
+//                                                     or of all interleaved planes, wz_unit_planes)
 //   then                     FwdParams params[count]
 struct BatchTable {
-    unsigned long long counter[wz::kIoModes];  // queue head per I/O mode, zeroed by a kernel before every run
-    int64_t first[wz::kIoModes + 1];           // items of mode m: [first[m], first[m + 1])
+    int64_t first[wz::kIoModes + 1];   // units of mode m: [first[m], first[m + 1])
     int64_t total_items;
+    int32_t slots[wz::kIoModes];       // tickets per unit of mode m: its largest plane count per unit
     int32_t count;
     int32_t pad0;
     int64_t params_offset;
@@ -80,6 +81,9 @@ inline int wz_grid_x(int64_t strips, bool share)
     const int64_t bx = (strips + kWavesPerBlock - 1) / kWavesPerBlock;
     return (int)(share ? (bx + kXcds - 1) / kXcds * kXcds : bx);
 }
+
+// planes of a unit: the same strip of an image's interleaved planes
+__host__ __device__ inline int wz_unit_planes(const wz::FwdJob& jb) { return jb.share ? jb.C : 1; }
 
 // Launches of one I/O mode (weno_zoom.hip, compiled once per mode): one doubling
 // of a job with its beta mode, columns per lane and strip height, and a batch

@@ -2,6 +2,7 @@
 // is compiled once for each value of WENO_IO (kIo* of weno_fwd.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "weno_fwd.h"
@@ -36,11 +37,11 @@ __device__ __forceinline__ StripCtx make_ctx(const FwdJob& jb, int n, int c, flo
 }
 
 // this wave's LDS rows for staged stores
-template <int COLS, int IO>
+template <int COLS, int IO, int WAVES = kWavesPerBlock>
 __device__ __forceinline__ float* wave_stage()
 {
     if constexpr (io_out_staged(IO)) {
-        __shared__ __align__(16) float rows[kWavesPerBlock * stage_floats<COLS, IO>()];
+        __shared__ __align__(16) float rows[WAVES * stage_floats<COLS, IO>()];
         return rows + (threadIdx.x >> 6) * stage_floats<COLS, IO>();
     } else {
         return nullptr;
@@ -120,51 +121,70 @@ __global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJo
     }
 }
 
-// Persistent kernel over a work queue of strips of many images, those of one
-// I/O mode (a kernel that switched between all modes took the registers of the
-// largest: 176 VGPRs, two waves per SIMD).  Item i of image k covers plane (i / per_plane) and strip (i % per_plane); images are
-// stored in the table largest first, so the queue drains big items early.
-// The table is read-only during the launch and the queue head is reached
-// through its own pointer, so table reads compile to scalar loads.
+// Persistent kernel over the strips of many images, those of one I/O mode (a
+// kernel that switched between all modes took the registers of the largest:
+// 176 VGPRs, two waves per SIMD).  A unit is one strip of a plane, or of all
+// the interleaved planes of an image.  One workgroup fills a compute unit (three
+// waves per SIMD, four with one column per lane); workgroup g takes units g,
+// g + grid, ..., and its waves share them out through a ticket in LDS, a ticket
+// being a plane of a unit (`slots` per unit, the largest plane count of the
+// mode's units; a smaller unit's spare tickets are empty).  The planes of a
+// strip, which fill the same lines with a byte in three each, then run side by
+// side on one compute unit, and the lines leave its L2 whole.  The work is
+// vector issue, the same on every compute unit, and the images are stored
+// largest first and in bands of nearly equal height, so fixed shares come out
+// even; within a compute unit they would not (a SIMD serves its oldest wave
+// first: workgroups of four waves with a ticket each, 2663 us for the 512
+// images below).  A queue for the whole device does not pay: a ticket drawn by
+// atomics on one address takes ~14 ns, one after another, and each wave's
+// last, empty one too (24 uint8 HWC images of 85 to 415 squared 82 -> 49 us
+// in the same strips, 512 of 32 to 1024 squared 2540 -> 2424).
+template <int COLS>
+constexpr int batch_waves() { return COLS == 2 ? 12 : 16; }
+
 template <int COLS, int BETA, int IO>
-__global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_batched_kernel(const BatchTable* __restrict__ tab,
-                                                                                 unsigned long long* __restrict__ counter,
-                                                                                 int rows_per_strip)
+__global__ __launch_bounds__(kWave * batch_waves<COLS>()) void zoom2x_batched_kernel(const BatchTable* __restrict__ tab)
 {
+    __shared__ int next;
     const int lane = threadIdx.x & (kWave - 1);
-    const int count = tab->count;
-    const int64_t first = tab->first[IO], total = tab->first[IO + 1];   // this mode's items
+    const int count = tab->count, slots = tab->slots[IO];
+    const int64_t first = tab->first[IO], last = tab->first[IO + 1];   // this mode's units
     const FwdJob* __restrict__ jobs = batch_jobs(tab);
     const int64_t* __restrict__ prefix = batch_prefix(tab);
-    float* const stage = wave_stage<COLS, IO>();
+    float* const stage = wave_stage<COLS, IO, batch_waves<COLS>()>();
+    if (threadIdx.x == 0) next = 0;
+    __syncthreads();
     for (;;) {
-        unsigned long long got = 0;
-        if (lane == 0) got = atomicAdd(counter, 1ull);
+        int got = 0;
+        if (lane == 0) got = atomicAdd(&next, 1);
         // broadcast lane 0's ticket as a provably uniform (scalar) value, so the
         // image table is read with scalar loads and the buffer resources stay
         // in SGPRs
-        const uint32_t lo32 = __builtin_amdgcn_readfirstlane((uint32_t)got);
-        const uint32_t hi32 = __builtin_amdgcn_readfirstlane((uint32_t)(got >> 32));
-        const int64_t item = first + (int64_t)(((unsigned long long)hi32 << 32) | lo32);
-        if (item >= total) break;  // every wave reaches this exit
-        // image k with prefix[k] <= item < prefix[k+1]
+        const int ticket = __builtin_amdgcn_readfirstlane(got);
+        const int turn = ticket / slots, slot = ticket - turn * slots;
+        const int64_t unit = first + blockIdx.x + (int64_t)turn * gridDim.x;
+        if (unit >= last) break;  // every wave reaches this exit
+        // image k with prefix[k] <= unit < prefix[k+1]
         int lo = 0, hi = count - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (prefix[mid] <= item) lo = mid; else hi = mid - 1;
+            if (prefix[mid] <= unit) lo = mid; else hi = mid - 1;
         }
         const FwdJob jb = jobs[lo];
-        const int64_t local = item - prefix[lo];
+        const int together = wz_unit_planes(jb);
+        if (slot >= together) continue;
+        const int64_t local = unit - prefix[lo];
         const int per_plane = jb.strips_x * jb.strips_y;
-        const int plane = (int)(local / per_plane);
-        const int wv = (int)(local - (int64_t)plane * per_plane);
+        const int group = (int)(local / per_plane);
+        const int wv = (int)(local - (int64_t)group * per_plane);
+        const int plane = group * together + slot;
         const int sy = wv / jb.strips_x;
         const int sx = wv - sy * jb.strips_x;
         const int n = plane / jb.C, c = plane - n * jb.C;
         const FwdParams P = batch_params(tab)[lo];
         const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
-        const int R0 = sy * rows_per_strip;
-        const int R1 = min(R0 + rows_per_strip, jb.H);
+        const int R0 = sy * jb.rows;
+        const int R1 = min(R0 + jb.rows, jb.H);
         zoom_strip<COLS, BETA, IO>(cx, P, sx * strip_own<COLS>(), R0, R1, stage);
     }
 }
@@ -214,17 +234,14 @@ hipError_t launch_single(const FwdJob& jb, const FwdParams& P, int rows, hipStre
     return hipGetLastError();
 }
 
-// persistent launch: as many workgroups as the device holds, no more than there
-// are items for
+// persistent launch: a workgroup per compute unit, no more than there are units
+// for
 template <int COLS, int BETA, int IO>
 hipError_t launch_batched(const weno_batch_plan_t* plan, hipStream_t st)
 {
-    int64_t blocks = (int64_t)wz_device_cus() * resident_blocks<COLS, BETA, IO>();
-    const int64_t by_work = (plan->total_items + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (blocks > by_work) blocks = by_work;
-    BatchTable* const tab = (BatchTable*)plan->d_workspace;
-    hipLaunchKernelGGL((zoom2x_batched_kernel<COLS, BETA, IO>), dim3((unsigned)blocks), dim3(kBlock), 0, st,
-                       (const BatchTable*)tab, &tab->counter[IO], plan->rows_per_strip);
+    const int64_t blocks = std::min<int64_t>(wz_device_cus(), plan->total_items);
+    hipLaunchKernelGGL((zoom2x_batched_kernel<COLS, BETA, IO>), dim3((unsigned)blocks),
+                       dim3(kWave * batch_waves<COLS>()), 0, st, (const BatchTable*)plan->d_workspace);
     return hipGetLastError();
 }
 
