@@ -59,8 +59,10 @@ class Params:
     def _build(self) -> WenoParams:
         if self.boundary not in _BOUNDARY:
             raise ValueError("boundary must be 'clamp' or 'external' (got %r)" % (self.boundary,))
-        return WenoParams(float(self.beta), float(self.k_eps), float(self.h), float(self.nbw),
-                          _BOUNDARY[self.boundary])
+        p = WenoParams(float(self.beta), float(self.k_eps), float(self.h), float(self.nbw),
+                       _BOUNDARY[self.boundary])
+        p.address = ctypes.addressof(p)   # read by the native call path while p is alive
+        return p
 
     def c(self) -> WenoParams:
         """The C struct; built once per distinct parameter set."""
@@ -115,6 +117,18 @@ def _desc(t: torch.Tensor) -> WenoTensor:
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
+# Call path of plain tensors in the common layouts (csrc/weno_native.c): None
+# from it means that the call goes the general way below.
+try:
+    from . import _native
+except ImportError:
+    _native = None
+if _native is not None and _raw_stream is not None:
+    _native.init(torch.uint8, torch.float32, torch.empty, _raw_stream, torch.Tensor)
+else:
+    _native = None
+
+
 def _stream(device) -> int:
     """Handle of torch's current HIP stream on `device` (a cuda device)."""
     if _raw_stream is not None:
@@ -144,6 +158,12 @@ def zoom2x_(x: torch.Tensor, out: torch.Tensor, params: Params | None = None, *,
             h=1.0, nbw=-1.0, boundary="clamp") -> torch.Tensor:
     """One WD-WENO doubling of x into the caller's `out` (..., 2H, 2W)."""
     p = _params(params, beta, k_eps, h, nbw, boundary)
+    if _native is not None:
+        rc = _native.zoom2x_(_lib.lib().address["weno_zoom2x"], p.address, x, out)
+        if rc is not None:
+            if rc != _lib.WENO_OK:
+                _lib.check(rc, "weno_zoom2x")
+            return out
     s, d = _desc(x), _desc(out)
     _lib.check(_lib.lib().weno_zoom2x(ctypes.byref(s), ctypes.byref(d), ctypes.byref(p), _stream(x.device)),
                "weno_zoom2x")
@@ -158,6 +178,13 @@ def zoom2x(x: torch.Tensor, params: Params | None = None, *, out_dtype=None, bet
     x's dtype) selects uint8 or float32 output.  boundary="external": x is a
     view into a larger array and its 4 rows/columns before and 5 after are
     the samples beyond the plane (the paper's function tests pass f there)."""
+    if _native is not None:
+        p = _params(params, beta, k_eps, h, nbw, boundary)
+        out = _native.zoom2x(_lib.lib().address["weno_zoom2x"], p.address, x, out_dtype)
+        if out is not None:
+            if type(out) is int:
+                _lib.check(out, "weno_zoom2x")
+            return out
     out = _empty_like_layout(x, 2, out_dtype or x.dtype)
     return zoom2x_(x, out, params, beta=beta, k_eps=k_eps, h=h, nbw=nbw, boundary=boundary)
 
@@ -253,6 +280,12 @@ def zoom2x_backward(x: torch.Tensor, grad_y: torch.Tensor, params: Params | None
             raise ValueError("out must be float32 of shape %s (got %s %s)" % (tuple(x.shape), out.dtype,
                                                                                tuple(out.shape)))
         gx = out
+    if _native is not None:
+        rc = _native.zoom2x_backward(_lib.lib().address["weno_zoom2x_backward"], p.address, x, grad_y, gx)
+        if rc is not None:
+            if rc != _lib.WENO_OK:
+                _lib.check(rc, "weno_zoom2x_backward")
+            return gx
     a, g, o = _desc(x), _desc(grad_y), _desc(gx)
     _lib.check(_lib.lib().weno_zoom2x_backward(ctypes.byref(a), ctypes.byref(g), ctypes.byref(o), ctypes.byref(p),
                                                _stream(x.device)), "weno_zoom2x_backward")

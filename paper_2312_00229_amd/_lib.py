@@ -114,6 +114,9 @@ def lib():
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
+        # addresses for the native call path
+        L.address = {name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
+                     for name in ("weno_zoom2x", "weno_zoom2x_backward")}
         _lib = L
     return _lib
 

@@ -1,4 +1,5 @@
-"""Build the HIP library in-tree: hipcc for gfx950 -> paper_2312_00229_amd/libweno_zoom.so.
+"""Build the HIP library in-tree: hipcc for gfx950 -> paper_2312_00229_amd/libweno_zoom.so,
+and the binding's call path, gcc -> _native.so.
 
 Flags: -O3, FP contraction off (every fused multiply-add in the kernels is
 written explicitly, so the operation sequence -- and hence every bit of the
@@ -10,6 +11,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -18,6 +20,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libweno_zoom.so")
+NATIVE = os.path.join(PKG, "_native.so")   # the binding's call path (CPython extension)
 # (source, macros, object name): the doubling's kernels compile once per I/O
 # mode (kIo* of weno_fwd.h), so that the compilations run side by side
 OBJECTS = [("weno_zoom.hip", ["-DWENO_IO=%d" % io], "weno_zoom%d" % io) for io in range(8)] + [
@@ -57,7 +60,22 @@ def _compile(flags, out_dir, verbose):
         return list(pool.map(one, OBJECTS))
 
 
+def build_native(verbose: bool = False) -> str:
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CC") or "gcc", "-O2", "-shared", "-fPIC", "-Wall", "-I" + sysconfig.get_paths()["include"],
+           "-I" + INCLUDE, os.path.join(CSRC, "weno_native.c"), "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("building %s failed" % NATIVE)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 def build(verbose: bool = False) -> str:
+    build_native(verbose)
     tmp = LIB + ".tmp%d" % os.getpid()
     with tempfile.TemporaryDirectory() as objs_dir:
         objs = _compile(["-O3"], objs_dir, verbose)
