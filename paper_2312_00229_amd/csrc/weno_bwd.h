@@ -204,22 +204,21 @@ __device__ __forceinline__ float cand_h(float ddh, float m) { return __builtin_f
 // differences ddf, ddb.  Returns the gradients at x0 (s0 = ga_f + gb_b), x1
 // (s1 = gb_f + ga_b), x2 (cf) and x-1 (cb).  A stencil (a, b, c) with
 // candidate seed gp and seed gs of its scaled indicator gives
-//   ga = 3/8 gp + gs (ddh - f),  gb = 3/4 gp + gs (f - 2 ddh),  gc = -1/8 gp + gs ddh;
-// written per line rather than per stencil, the slope terms of the two
-// stencils fold into one product F = f (gs_f + gs_b), and with E = gs ddh
-//   s0 = 3/8 gp_f + 3/4 gp_b + E_f - 2 E_b - F
-//   s1 = 3/4 gp_f + 3/8 gp_b - 2 E_f + E_b + F
-//   cf = -1/8 gp_f + E_f,   cb = -1/8 gp_b + E_b
-// (14 operations against 20 for two stencils and the two sums).
-__device__ __forceinline__ void line_adj(float gpf, float gsf, float ddf, float gpb, float gsb, float ddb, float f,
+//   ga = 3/8 gp + gs (ddh - f),  gb = 3/4 gp + gs (f - 2 ddh),  gc = -1/8 gp + gs ddh.
+// The seeds come as g8 = -gp/8 (the factor folds into the upstream gradient),
+// so that gc is one operation; written with cf and cb, and with
+// F = f (gs_f + gs_b) and H = -4 (g8_f + g8_b) = (gp_f + gp_b)/2,
+//   s0 = cf - 2 cb + H - F,   s1 = cb - 2 cf + H + F
+// (11 operations for the pair, against 14 for the two stencils written out
+// per line and 20 for each on its own).
+__device__ __forceinline__ void line_adj(float g8f, float gsf, float ddf, float g8b, float gsb, float ddb, float f,
                                          float& s0, float& s1, float& cf, float& cb)
 {
-    const float ef = gsf * ddf, eb = gsb * ddb;
-    const float F = (gsf + gsb) * f;
-    s0 = __builtin_fmaf(gpf, 0.375f, __builtin_fmaf(gpb, 0.75f, __builtin_fmaf(eb, -2.0f, ef - F)));
-    s1 = __builtin_fmaf(gpf, 0.75f, __builtin_fmaf(gpb, 0.375f, __builtin_fmaf(ef, -2.0f, eb + F)));
-    cf = __builtin_fmaf(gpf, -0.125f, ef);
-    cb = __builtin_fmaf(gpb, -0.125f, eb);
+    cf = __builtin_fmaf(gsf, ddf, g8f);
+    cb = __builtin_fmaf(gsb, ddb, g8b);
+    const float F = (gsf + gsb) * f, H8 = g8f + g8b;
+    s0 = __builtin_fmaf(cb, -2.0f, cf + __builtin_fmaf(H8, -4.0f, -F));
+    s1 = __builtin_fmaf(cf, -2.0f, cb + __builtin_fmaf(H8, -4.0f, F));
 }
 
 typedef float bwd_f32x4 __attribute__((ext_vector_type(4)));
@@ -256,7 +255,8 @@ __device__ __forceinline__ void bwd_strip(const BwdCtx& cx, const FwdParams& P, 
     constexpr uint32_t kOobCol = 0x7fffffffu, kOobRow = 0x80000000u;
     const uint32_t gyoffA = colin ? (uint32_t)(2 * jc) * cx.gy_w : kOobCol;        // column 2J
     const uint32_t gyoffB = colin ? (uint32_t)(2 * jc + 1) * cx.gy_w : kOobCol;    // column 2J+1
-    const uint32_t gxoff = (uint32_t)jc * cx.gx_w;
+    // lanes that own no column store through an offset the buffer unit drops
+    const uint32_t gxoff = own ? (uint32_t)jc * cx.gx_w : kOobCol;
     const bool first_strip = c0 == 0;
     const bool last_strip = c0 + width >= W;
     const bool top = R0 == 0, bottom = R1 == H;
@@ -493,12 +493,12 @@ __device__ __forceinline__ void bwd_strip(const BwdCtx& cx, const FwdParams& P, 
         float dcV_0 = 0.0f;
         if constexpr (FULL) {
         // -beta folds into the seed first (exact for beta = 1 and 2)
-        const float gAb = -beta * gA, gBb = -beta * gB;
+        const float gAb = -beta * gA, gBb = -beta * gB, gA8 = -0.125f * gA, gB8 = -0.125f * gB;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            gpA[k] = gA * omA[k];
+            gpA[k] = gA8 * omA[k];   // -1/8 of the candidate seeds, here and below (line_adj)
             gtA[k] = gAb * dkA[k];
-            gpB[k] = gB * omB[k];
+            gpB[k] = gB8 * omB[k];
             gtB[k] = gBb * dkB[k];
         }
 #pragma unroll
@@ -544,10 +544,10 @@ __device__ __forceinline__ void bwd_strip(const BwdCtx& cx, const FwdParams& P, 
         }
 
         // ======================= phase-1 seeds at x row s-2 =======================
-        const float gXc = accX_m2 + gXu, gXb = -beta * gXc;
+        const float gXc = accX_m2 + gXu, gXb = -beta * gXc, gX8 = -0.125f * gXc;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            gpX_m2[k] = gXc * omXr[k];
+            gpX_m2[k] = gX8 * omXr[k];
             gtX_m2[k] = gXb * dkXr[k];
         }
 
@@ -578,6 +578,14 @@ __device__ __forceinline__ void bwd_strip(const BwdCtx& cx, const FwdParams& P, 
 
         // ======================= dL/dV row s-4 is complete =======================
         if constexpr (P1) {
+            // The branches of the edge folds end a basic block here.  Sums that
+            // later steps read would be moved behind them, away from the lane
+            // shifts they take as DPP operands, which then stay as moves (12
+            // more per step, 220 VGPRs against 189): pin them in this block.
+            asm volatile("" : "+v"(accV_m3), "+v"(accV_m2), "+v"(accV_m1), "+v"(accV_0), "+v"(accV_p1),
+                         "+v"(accX_m1), "+v"(accX_0), "+v"(accX_p1));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(qA[k]), "+v"(qB[k]), "+v"(hA0[k]), "+v"(hB1[k]));
             const int r = s - 4;
             float val = accV_m4 + gVu;
             // clamped columns: padded columns -4..-1 fold onto column 0, W..W+4 onto W-1
@@ -596,17 +604,17 @@ __device__ __forceinline__ void bwd_strip(const BwdCtx& cx, const FwdParams& P, 
             // clamped rows: rows -4..-1 fold onto row 0, rows H..H+4 onto row
             // H-1; interior steps store rows in [R0, R1) that fold nothing
             if constexpr (INTERIOR) {
-                if (own) stG(r, val);
+                stG(r, val);
             } else if (top && r <= 0 && r < H - 1) {
                 if (r < 0) {
                     if (r >= -4) fold_top += val;   // padded rows -4..-1; earlier rows are pipeline fill
-                } else if (own) {
+                } else {
                     stG(0, val + fold_top);
                 }
             } else if (bottom && r >= H - 1) {
                 held += (r == H - 1 && top && H == 1) ? val + fold_top : val;
             } else if (r >= R0 && r < R1) {
-                if (own) stG(r, val);
+                stG(r, val);
             }
         }
         }   // FULL
@@ -697,7 +705,7 @@ __device__ __forceinline__ void bwd_strip(const BwdCtx& cx, const FwdParams& P, 
     for (; s <= s_end; ++s) step(s, Full{}, P1All{}, 0);
     if (bottom) {
         const int r = H - 1;
-        if (r >= R0 && own) stG(r, held);
+        if (r >= R0) stG(r, held);
     }
 }
 
