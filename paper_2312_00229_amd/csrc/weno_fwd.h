@@ -237,9 +237,11 @@ __device__ __forceinline__ void buf_st_f32(float v, rsrc_t r, uint32_t voff, uin
 // the default write-back policy: there the flush is a small part of the
 // launch, and a store written through completes later, which delays the
 // waits of the loads issued after it (3x4320x7680: 0.524 -> 0.544 ms
-// written through).  Byte stores always keep it: their lines are filled in
-// pieces by several waves, and writing every piece through costs far more
-// than the flush (uint8 HWC 1080p: 69.7 against 43.5 us).
+// written through).  Packed byte rows are written through as well (1080p RGB
+// uint8 planar: 38.0-40.2 -> 36.6 us, one plane 17.0 -> 16.2).  Stores of spread
+// elements keep write-back: their lines are filled in pieces by several
+// waves, and writing every piece through costs far more than the flush (uint8
+// HWC 1080p: 69.7 against 43.5 us).
 constexpr int kStRows = 16;
 
 template <int POLICY = 0>
@@ -256,13 +258,15 @@ __device__ __forceinline__ void buf_st_f32x4(f32x4 v, rsrc_t r, uint32_t voff, u
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)voff, (int)soff, POLICY);
 }
+template <int POLICY = 0>
 __device__ __forceinline__ void buf_st_u16(uint32_t v, rsrc_t r, uint32_t voff, uint32_t soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)voff, (int)soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)voff, (int)soff, POLICY);
 }
+template <int POLICY = 0>
 __device__ __forceinline__ void buf_st_u32(uint32_t v, rsrc_t r, uint32_t voff, uint32_t soff)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)voff, (int)soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)voff, (int)soff, POLICY);
 }
 __device__ __forceinline__ void buf_st_u8(uint32_t v, rsrc_t r, uint32_t voff, uint32_t soff)
 {
@@ -379,15 +383,15 @@ __device__ __forceinline__ void store_quads(const StripCtx& cx, int R, const Str
             w1 = quant_u8(d[k], 2 * k + 1, quant_u8(c[k], 2 * k, w1));
         }
         if constexpr (COLS == 2) {
-            buf_st_u32(w0, cx.dst, L.st_vec, r0);
-            buf_st_u32(w1, cx.dst, L.st_vec, r1);
+            buf_st_u32<ST>(w0, cx.dst, L.st_vec, r0);
+            buf_st_u32<ST>(w1, cx.dst, L.st_vec, r1);
             if (L.any_half) {
-                buf_st_u16(w0, cx.dst, L.st_half, r0);
-                buf_st_u16(w1, cx.dst, L.st_half, r1);
+                buf_st_u16<ST>(w0, cx.dst, L.st_half, r0);
+                buf_st_u16<ST>(w1, cx.dst, L.st_half, r1);
             }
         } else {
-            buf_st_u16(w0, cx.dst, L.st_vec, r0);
-            buf_st_u16(w1, cx.dst, L.st_vec, r1);
+            buf_st_u16<ST>(w0, cx.dst, L.st_vec, r0);
+            buf_st_u16<ST>(w1, cx.dst, L.st_vec, r1);
         }
     } else if constexpr (io_out_u8(IO)) {
         // one byte per store, the odd columns through the scalar row offset
@@ -641,7 +645,7 @@ template <int COLS, int BETA, int IO, bool PACED = false>
 __device__ __forceinline__ void zoom_strip(const StripCtx& cx, const FwdParams& P, int c0, int R0, int R1,
                                            float* stage = nullptr)
 {
-    constexpr int ST = PACED && !io_out_spread(IO) && !io_out_u8(IO) ? kStRows : 0;
+    constexpr int ST = PACED && !io_out_spread(IO) ? kStRows : 0;
     constexpr int HALO_L = 4;
     constexpr int OWN = strip_own<COLS>();
     const int lane = threadIdx.x & (kWave - 1);
