@@ -311,7 +311,11 @@ constexpr int kStartCost = 4;
 // columns per band, 80.1 -> 71.9 predicted.
 constexpr int kTailStretch = 7;
 
-void wz_auto_config(int64_t planes, int H, int W, bool share, int* rows, int* cols, int* tail_rows)
+// spread_bytes: a destination of bytes with spread columns, whose two-column
+// kernels store eight elements a row: an iteration costs ~1.09 of the table's
+// (3x1024x1024 float32 to uint8 HWC: 20-row one-column strips 23.4 us, 14-row
+// two-column ones, the pick without the factor, 24.0).
+void wz_auto_config(int64_t planes, int H, int W, bool share, bool spread_bytes, int* rows, int* cols, int* tail_rows)
 {
     const int64_t cus = wz_device_cus();
     double best = 0.0;
@@ -330,7 +334,8 @@ void wz_auto_config(int64_t planes, int H, int W, bool share, int* rows, int* co
             r = r < 4 ? 4 : (r > 4096 ? 4096 : r);
             const int64_t blocks = planes * wz_grid_x(strips_x * ((H + r - 1) / r), share);
             const int64_t mm = (blocks + cus - 1) / cus;
-            const double cost = (double)mm * (r + kStartCost) * iteration_cost(c, mm);
+            const double cost =
+                (double)mm * (r + kStartCost) * iteration_cost(c, mm) * (spread_bytes && c == 2 ? 1.09 : 1.0);
             if (best == 0.0 || cost < best) {
                 best = cost;
                 best_rows = r;
@@ -378,7 +383,8 @@ void wz_config_for(const weno_tensor_t* src, const weno_tensor_t* dst, int* rows
     *tail_rows = 0;
     const bool share = planes_share_lines(src->c, src->sc, src->sh) || planes_share_lines(dst->c, dst->sc, dst->sh);
     if (*rows == 0 || *cols == 0) {
-        wz_auto_config((int64_t)src->n * src->c, src->h, src->w, share, rows, cols, tail_rows);
+        wz_auto_config((int64_t)src->n * src->c, src->h, src->w, share, dst->dtype == WENO_U8 && dst->sw != 1, rows,
+                       cols, tail_rows);
         if (dst->sw != 1) *tail_rows = 0;   // tail strips store contiguous columns only
     }
 }
