@@ -14,8 +14,7 @@ tuning never leaves a shape slower than the default.
 `tune_backward` picks the adjoint kernel's strip height (its own setting;
 it always runs one column per lane; the automatic height is a candidate,
 recorded as 0), checking that the gradient stays bit-identical.  `tune_batched` does the same for a
-batched plan (the persistent kernel over a
-work queue): plans capture the configuration when they are made, so it builds
+batched plan (the persistent kernel): plans capture the configuration when they are made, so it builds
 one plan per candidate, checks that all outputs stay bit-identical and leaves
 the fastest configuration applied for the plans made afterwards.
 
