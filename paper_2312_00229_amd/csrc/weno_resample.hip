@@ -412,10 +412,9 @@ __global__ __launch_bounds__(kBlock) void wave_resample_kernel(WaveArgs a)
     const int xcd = b % kXcds, kb = b / kXcds;
     int plane, blk;
     if (a.share) {
-        const int per_xcd = nb / (kXcds * a.planes);
-        const int n = kb / (per_xcd * a.C), r = kb - n * per_xcd * a.C;
-        plane = n * a.C + r % a.C;
-        blk = xcd * per_xcd + r / a.C;
+        const int per_xcd = nb / (kXcds * a.C);
+        plane = blockIdx.y * a.C + kb % a.C;
+        blk = xcd * per_xcd + kb / a.C;
     } else {
         plane = a.reverse ? a.planes - 1 - blockIdx.y : blockIdx.y;
         blk = xcd * (nb / kXcds) + min(xcd, nb % kXcds) + kb;
@@ -927,8 +926,8 @@ int launch_wave(const weno_tensor_t* src, const weno_tensor_t* dst, const WaveSh
     a.beta = p->beta;
     const int64_t waves = (int64_t)((dst->h + a.run - 1) / a.run) * fs.ctiles;
     int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (a.share) blocks = (blocks + kXcds - 1) / kXcds * kXcds * a.planes;
-    const dim3 grid((unsigned)blocks, a.share ? 1u : (unsigned)a.planes);
+    if (a.share) blocks = (blocks + kXcds - 1) / kXcds * kXcds * a.C;
+    const dim3 grid((unsigned)blocks, (unsigned)(a.share ? a.planes / a.C : a.planes));
     if (p->beta == 2.0f) launch_wave_beta<2>(a, fs.m, in_u8, out_u8, grid, st);
     else launch_wave_beta<kBetaGeneral>(a, fs.m, in_u8, out_u8, grid, st);
     const hipError_t e = hipGetLastError();

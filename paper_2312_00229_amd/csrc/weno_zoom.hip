@@ -63,8 +63,8 @@ __global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJo
     // mod 8, so the XCD of a strip rotates from plane to plane, which spreads
     // the planes' workgroups evenly over the XCDs.  With tail strips the grid
     // is one-dimensional and every XCD gets a contiguous range of waves, plane
-    // after plane.  For images whose planes are interleaved (HWC) the grid is
-    // one-dimensional too, a multiple of 8 workgroups per plane, and on each
+    // after plane.  For images whose planes are interleaved (HWC) a row of the grid
+    // is an image, a multiple of 8 workgroups per plane, and on each
     // XCD a strip's workgroups of all the planes follow each other: the lines
     // the planes share meet in one L2 while they are there, instead of reaching
     // HBM once per plane with a third of their bytes each (1080p RGB uint8:
@@ -101,12 +101,11 @@ __global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJo
     } else {
         int n, c, w = wave;
         if (jb.share) {
-            // on each XCD: image by image, workgroup by workgroup, plane by plane
-            const int per_xcd = nb / (kXcds * jb.planes);
-            n = k / (per_xcd * jb.C);
-            const int r = k - n * per_xcd * jb.C;
-            c = r % jb.C;
-            w = __builtin_amdgcn_readfirstlane((xcd * per_xcd + r / jb.C) * kWavesPerBlock + (threadIdx.x >> 6));
+            // image blockIdx.y; on each XCD workgroup by workgroup, plane by plane
+            const int per_xcd = nb / (kXcds * jb.C);
+            n = blockIdx.y;
+            c = k % jb.C;
+            w = __builtin_amdgcn_readfirstlane((xcd * per_xcd + k / jb.C) * kWavesPerBlock + (threadIdx.x >> 6));
         } else {
             n = blockIdx.y / jb.C;
             c = blockIdx.y - n * jb.C;
@@ -213,7 +212,7 @@ template <int COLS, int BETA, int IO>
 hipError_t launch_single(const FwdJob& jb, const FwdParams& P, int rows, hipStream_t st)
 {
     dim3 grid(wz_grid_x((int64_t)jb.strips_x * jb.strips_y, jb.share), jb.planes);
-    if (jb.share) grid = dim3(grid.x * grid.y, 1);   // the planes' workgroups interleaved (zoom2x_kernel)
+    if (jb.share) grid = dim3(grid.x * jb.C, jb.planes / jb.C);   // an image's planes interleaved (zoom2x_kernel)
     if constexpr (COLS == 2 && !io_out_spread(IO)) {
         if (jb.tail_rows > 0) {  // one wave index across the planes
             const int64_t waves = (int64_t)jb.planes * ((int64_t)jb.strips_x * jb.strips_y + jb.tail_bands);
