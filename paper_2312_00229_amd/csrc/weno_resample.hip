@@ -365,8 +365,8 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(ColPassArgs a, const Sam
 // the same bits.
 //
 // What bounds it is vector issue where it enlarges and memory where it
-// shrinks (3x4319x7679 -> 3240x5760: 146 us; 97 us with all reads and writes
-// hitting the caches, 120 with the writes alone doing so; 4.3 TB/s against the
+// shrinks (3x4319x7679 -> 3240x5760: 139 us; 97 us with all reads and writes
+// hitting the caches, 120 with the writes alone doing so; 4.5 TB/s against the
 // 5.1 of a plain copy), so nothing may hold a wave up.  The LDS row is the
 // wave's own, and LDS serves a wave in order: there is no barrier.  The wave
 // walks the input intervals one by one with kAhead rows requested ahead; the
@@ -811,12 +811,21 @@ int launch_cols_pass(const uint8_t* tmp, uint32_t t_h, const weno_tensor_t* dst,
 // balanced.  Slots and columns both cost a wave-wide evaluation per row,
 // whether all lanes need it or not, so the pair with the fewest per row is
 // taken.  m = 0: no tile of 64 columns fits 256 slots (width ratios above ~4).
+// lines: the rows of the output start on lines of 128 bytes and hold 32 values
+// in each (launch_wave).  Tiles whose edges fall on lines leave no line to be
+// written in two parts by two waves: the width is rounded up to whole lines
+// where the span allows it, and such a tile is taken for up to 5 % more
+// evaluations (float32, three planes: 2160x3840 -> 3240x5760 23 tiles of 256
+// columns for 31 of 186, 91 -> 87 us; 2880x5120 -> 2160x3840 30 of 128 for 21
+// of 183, 65 -> 61; 4319x7679 -> 3240x5760 45 of 128 for 31 of 186, 143 -> 139.
+// At 10 % 2160x3840 -> 2880x5120 takes 80 tiles of 64, 72 -> 77).
 struct WaveShape {
     int m, tw, ctiles;
 };
 
-WaveShape wave_shape(int n_in, int n_out)
+WaveShape wave_shape(int n_in, int n_out, bool lines = false)
 {
+    constexpr int64_t kLine = 32;
     const int64_t num = n_in > 1 ? n_in - 1 : 0, den = n_out > 1 ? n_out - 1 : 1;
     const int64_t min_tw = n_out < kWave ? n_out : kWave;
     WaveShape best = {0, 0, 0};
@@ -827,10 +836,17 @@ WaveShape wave_shape(int n_in, int n_out)
         if (twmax > kWave * kTileQ) twmax = kWave * kTileQ;
         for (int64_t q = 1; q <= kTileQ; ++q) {
             const int64_t tw = twmax < kWave * q ? twmax : kWave * q;
-            const int64_t tiles = (n_out + tw - 1) / tw;
-            const int64_t cost = tiles * (m + q);
+            int64_t tiles = (n_out + tw - 1) / tw;
+            int64_t even = (n_out + tiles - 1) / tiles;
+            const int64_t whole = (even + kLine - 1) / kLine * kLine;
+            if (lines && whole <= tw) {
+                even = whole;
+                tiles = (n_out + even - 1) / even;
+            }
+            int64_t cost = 20 * tiles * (m + q);
+            if (lines && even % kLine != 0) cost += cost / 20;
             if (best.m == 0 || cost < best_cost) {
-                best = {m, (int)((n_out + tiles - 1) / tiles), (int)tiles};
+                best = {m, (int)even, (int)tiles};
                 best_cost = cost;
             }
         }
@@ -866,6 +882,13 @@ WaveRun wave_run(int out_h, int ctiles, int64_t planes)
     return {(int)(run < 12 ? 12 : (run > 18 ? 18 : run)), false};
 }
 
+// Are the rows of a float32 output dense and does each start on a line of 128 bytes?
+bool whole_lines(const weno_tensor_t* t)
+{
+    return t->dtype == WENO_F32 && t->sw == 1 && (uintptr_t)t->data % 128 == 0 && t->sh % 32 == 0 && t->sc % 32 == 0 &&
+           t->sn % 32 == 0;
+}
+
 template <int BETA, int M>
 void launch_wave_typed(const WaveArgs& a, bool in_u8, bool out_u8, dim3 grid, hipStream_t st)
 {
@@ -890,7 +913,7 @@ void launch_wave_beta(const WaveArgs& a, int m, bool in_u8, bool out_u8, dim3 gr
     }
 }
 
-int launch_wave(const weno_tensor_t* src, const weno_tensor_t* dst, const WaveShape& fs, const weno_params_t* p,
+int launch_wave(const weno_tensor_t* src, const weno_tensor_t* dst, WaveShape fs, const weno_params_t* p,
                  double h, bool reverse, hipStream_t st)
 {
     WaveArgs a;
@@ -913,11 +936,22 @@ int launch_wave(const weno_tensor_t* src, const weno_tensor_t* dst, const WaveSh
     a.in_w = src->w;
     a.out_h = dst->h;
     a.out_w = dst->w;
-    a.tw = fs.tw;
-    a.ctiles = fs.ctiles;
     a.planes = src->n * src->c;
     a.share = planes_share_lines(src->c, src->sc, src->sh) || planes_share_lines(dst->c, dst->sc, dst->sh);
-    const WaveRun wr = wave_run(dst->h, fs.ctiles, a.planes);
+    WaveRun wr = wave_run(dst->h, fs.ctiles, a.planes);
+    // Tiles of whole lines pay where the launch is large enough to wait for
+    // memory; a launch of one round waits for its waves (3x1080x1920 ->
+    // 1440x2560 float32: 40 tiles of 64 columns for 11 of 233, 19.9 -> 23.7 us).
+    if (!wr.paced && whole_lines(dst)) {
+        const WaveShape ls = wave_shape(src->w, dst->w, true);
+        const WaveRun lr = wave_run(dst->h, ls.ctiles, a.planes);
+        if (!lr.paced) {
+            fs = ls;
+            wr = lr;
+        }
+    }
+    a.tw = fs.tw;
+    a.ctiles = fs.ctiles;
     a.run = wr.rows;
     a.paced = wr.paced;
     a.reverse = reverse;
