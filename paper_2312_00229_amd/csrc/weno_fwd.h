@@ -46,6 +46,7 @@ constexpr int kWave = 64;
 constexpr int kWavesPerBlock = 4;
 constexpr int kBlock = kWave * kWavesPerBlock;
 constexpr int kXcds = 8;  // MI355X: accelerator complex dies, one L2 each
+constexpr int64_t kInfinityCache = 256ll << 20;  // MI355X: bytes of the memory-side cache
 
 // beta specialisations
 constexpr int kBetaGeneral = -1;
@@ -233,16 +234,25 @@ __device__ __forceinline__ void buf_st_f32(float v, rsrc_t r, uint32_t voff, uin
 // never read back by the launch; held dirty, it is written back only when the
 // launch ends, where every XCD's L2 is flushed before a dependent launch may
 // start, and that flush of up to 4 MB per XCD is time the launch adds after
-// its last wave (1080p RGB float32: 38.7 -> 36.4 us).  Longer launches keep
-// the default write-back policy: there the flush is a small part of the
-// launch, and a store written through completes later, which delays the
-// waits of the loads issued after it (3x4320x7680: 0.524 -> 0.544 ms
-// written through).  Packed byte rows are written through as well (1080p RGB
-// uint8 planar: 38.0-40.2 -> 36.6 us, one plane 17.0 -> 16.2).  Stores of spread
-// elements keep write-back: their lines are filled in pieces by several
-// waves, and writing every piece through costs far more than the flush (uint8
-// HWC 1080p: 69.7 against 43.5 us).
+// its last wave (1080p RGB float32: 38.7 -> 36.4 us).  Launches of
+// several rounds keep the default write-back policy: there the flush is a
+// small part of the launch, and a store written through completes later, which
+// delays the waits of the loads issued after it (3x4320x7680: 0.524 -> 0.544
+// ms written through).  So do float launches of one round that read and write
+// more than the Infinity Cache holds (kPacedBack): strips end inside a line,
+// and a part written through to HBM by itself costs more than the flush
+// (3x1600x2880, 276 MB: 88 us written through, 78 back; 3x2160x3584 136, 126;
+// one plane of 8192^2 362, 348; up to 252 MB, three planes of 2048^2, 65.5 and
+// 67.3).  Packed byte rows of one round are written through at every size (1080p
+// RGB uint8 planar: 38.0-40.2 -> 36.6 us, one plane 17.0 -> 16.2; 3x2160x3840
+// 125.3, 127.0 written back).  Stores of spread elements keep write-back: their
+// lines are filled in pieces by several waves, and writing every piece through
+// costs far more than the flush (uint8 HWC 1080p: 69.7 against 43.5 us).
 constexpr int kStRows = 16;
+
+// how a launch's waves go: in several rounds, or in one, paced (zoom_strip),
+// with whole output rows written through the L2 or back from it
+enum Pace { kRounds, kPacedThrough, kPacedBack };
 
 template <int POLICY = 0>
 __device__ __forceinline__ void buf_st_f32x2(float a, float b, rsrc_t r, uint32_t voff, uint32_t soff)
@@ -633,19 +643,20 @@ template <int COLS>
 constexpr int strip_own() { return COLS == 1 ? kWave - 9 : 2 * kWave - 10; }
 
 // Walk one strip: owned columns [c0, c0 + strip_own), output rows [R0, R1).
-// PACED: the launch runs as one round of waves (every wave resident from the
-// start): pace the waves that share a SIMD and write whole output rows
-// through the L2.  stage: the wave's stage_floats<COLS, IO>() floats of LDS, 16-byte
+// PACE: in a launch of one round of waves (every wave resident from the
+// start), the waves that share a SIMD are paced, and whole output rows are
+// written through the L2 unless kPacedBack.  stage: the wave's stage_floats<COLS, IO>() floats of LDS, 16-byte
 // aligned (two rows of 2*COLS outputs per lane; lanes that store nothing read
 // up to 8 floats past them).
 template <int COLS, int IO>
 constexpr int stage_floats() { return io_out_staged(IO) ? 2 * kWave * 2 * COLS + 16 : 0; }
 
-template <int COLS, int BETA, int IO, bool PACED = false>
+template <int COLS, int BETA, int IO, Pace PACE = kRounds>
 __device__ __forceinline__ void zoom_strip(const StripCtx& cx, const FwdParams& P, int c0, int R0, int R1,
                                            float* stage = nullptr)
 {
-    constexpr int ST = PACED && !io_out_spread(IO) ? kStRows : 0;
+    constexpr bool PACED = PACE != kRounds;
+    constexpr int ST = PACE == kPacedThrough && !io_out_spread(IO) ? kStRows : 0;
     constexpr int HALO_L = 4;
     constexpr int OWN = strip_own<COLS>();
     const int lane = threadIdx.x & (kWave - 1);

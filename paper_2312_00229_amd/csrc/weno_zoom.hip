@@ -52,7 +52,7 @@ __device__ __forceinline__ float* wave_stage()
 // (jb.tail_rows > 0) and one wave index across the planes
 // Two-column kernels are held to 168 VGPRs, three waves per SIMD: strided float
 // destinations would take 170 (two to four values spill).
-template <int COLS, int BETA, int IO, bool PACED, bool TAIL = false>
+template <int COLS, int BETA, int IO, Pace PACE, bool TAIL = false>
 __global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJob jb, FwdParams P, int rows_per_strip)
 {
     // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.
@@ -91,11 +91,11 @@ __global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJo
         if (w < n2) {
             const int sy = w / jb.strips_x, sx = w - sy * jb.strips_x;
             const int R0 = sy * rows_per_strip;
-            zoom_strip<2, BETA, IO, PACED>(cx, P, sx * strip_own<2>(), R0, min(R0 + rows_per_strip, jb.H),
+            zoom_strip<2, BETA, IO, PACE>(cx, P, sx * strip_own<2>(), R0, min(R0 + rows_per_strip, jb.H),
                                            stage);
         } else {
             const int R0 = (w - n2) * jb.tail_rows;
-            zoom_strip<1, BETA, IO, PACED>(cx, P, jb.strips_x * strip_own<2>(), R0, min(R0 + jb.tail_rows, jb.H),
+            zoom_strip<1, BETA, IO, PACE>(cx, P, jb.strips_x * strip_own<2>(), R0, min(R0 + jb.tail_rows, jb.H),
                                            stage);
         }
     } else {
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJo
         const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
         const int R0 = sy * rows_per_strip;
         const int R1 = min(R0 + rows_per_strip, jb.H);
-        zoom_strip<COLS, BETA, IO, PACED>(cx, P, sx * strip_own<COLS>(), R0, R1, stage);
+        zoom_strip<COLS, BETA, IO, PACE>(cx, P, sx * strip_own<COLS>(), R0, R1, stage);
     }
 }
 
@@ -198,7 +198,7 @@ int resident_blocks()
     int v = cache.load();
     if (v == 0) {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &v, reinterpret_cast<const void*>(zoom2x_kernel<COLS, BETA, IO, true>), kBlock, 0) != hipSuccess ||
+                &v, reinterpret_cast<const void*>(zoom2x_kernel<COLS, BETA, IO, kPacedThrough>), kBlock, 0) != hipSuccess ||
             v <= 0)
             v = 1;
         cache.store(v);
@@ -208,6 +208,26 @@ int resident_blocks()
 
 // A launch whose workgroups all fit on the device at once (one round) is
 // paced (zoom_strip); one of several rounds is not.
+template <int COLS, int BETA, int IO, bool TAIL>
+hipError_t launch_paced(const FwdJob& jb, const FwdParams& P, int rows, dim3 grid, hipStream_t st)
+{
+    const int64_t blocks = (int64_t)grid.x * grid.y;
+    if (blocks > (int64_t)resident_blocks<COLS, BETA, IO>() * wz_device_cus()) {
+        hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, kRounds, TAIL>), grid, dim3(kBlock), 0, st, jb, P, rows);
+        return hipGetLastError();
+    }
+    if constexpr (!io_out_u8(IO) && !io_out_spread(IO)) {
+        const int64_t px = (int64_t)jb.planes * jb.H * jb.W;
+        if (px * (io_in_u8(IO) ? 1 : 4) + 4 * px * 4 > kInfinityCache) {
+            hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, kPacedBack, TAIL>), grid, dim3(kBlock), 0, st, jb, P,
+                               rows);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, kPacedThrough, TAIL>), grid, dim3(kBlock), 0, st, jb, P, rows);
+    return hipGetLastError();
+}
+
 template <int COLS, int BETA, int IO>
 hipError_t launch_single(const FwdJob& jb, const FwdParams& P, int rows, hipStream_t st)
 {
@@ -217,20 +237,10 @@ hipError_t launch_single(const FwdJob& jb, const FwdParams& P, int rows, hipStre
         if (jb.tail_rows > 0) {  // one wave index across the planes
             const int64_t waves = (int64_t)jb.planes * ((int64_t)jb.strips_x * jb.strips_y + jb.tail_bands);
             grid = dim3((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock), 1);
-            if ((int64_t)grid.x <= (int64_t)resident_blocks<COLS, BETA, IO>() * wz_device_cus())
-                hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, true, true>), grid, dim3(kBlock), 0, st, jb, P, rows);
-            else
-                hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, false, true>), grid, dim3(kBlock), 0, st, jb, P,
-                                   rows);
-            return hipGetLastError();
+            return launch_paced<COLS, BETA, IO, true>(jb, P, rows, grid, st);
         }
     }
-    const int64_t blocks = (int64_t)grid.x * grid.y;
-    if (blocks <= (int64_t)resident_blocks<COLS, BETA, IO>() * wz_device_cus())
-        hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, true>), grid, dim3(kBlock), 0, st, jb, P, rows);
-    else
-        hipLaunchKernelGGL((zoom2x_kernel<COLS, BETA, IO, false>), grid, dim3(kBlock), 0, st, jb, P, rows);
-    return hipGetLastError();
+    return launch_paced<COLS, BETA, IO, false>(jb, P, rows, grid, st);
 }
 
 // persistent launch: a workgroup per compute unit, no more than there are units
