@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(ColPassArgs a, const Sam
 // the same bits.
 //
 // What bounds it is vector issue where it enlarges and memory where it
-// shrinks (3x4319x7679 -> 3240x5760: 139 us; 97 us with all reads and writes
+// shrinks (3x4320x7680 -> 3240x5760: 139 us; 97 us with all reads and writes
 // hitting the caches, 120 with the writes alone doing so; 4.5 TB/s against the
 // 5.1 of a plain copy), so nothing may hold a wave up.  The LDS row is the
 // wave's own, and LDS serves a wave in order: there is no barrier.  The wave
@@ -817,7 +817,7 @@ int launch_cols_pass(const uint8_t* tmp, uint32_t t_h, const weno_tensor_t* dst,
 // where the span allows it, and such a tile is taken for up to 5 % more
 // evaluations (float32, three planes: 2160x3840 -> 3240x5760 23 tiles of 256
 // columns for 31 of 186, 91 -> 87 us; 2880x5120 -> 2160x3840 30 of 128 for 21
-// of 183, 65 -> 61; 4319x7679 -> 3240x5760 45 of 128 for 31 of 186, 143 -> 139.
+// of 183, 65 -> 61; 4320x7680 -> 3240x5760 45 of 128 for 31 of 186, 143 -> 139.
 // At 10 % 2160x3840 -> 2880x5120 takes 80 tiles of 64, 72 -> 77).
 struct WaveShape {
     int m, tw, ctiles;
