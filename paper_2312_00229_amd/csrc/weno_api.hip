@@ -308,7 +308,9 @@ constexpr int kStartCost = 4;
 // each walks about as long as a two-column strip (a one-column iteration
 // costs ~0.59 of a two-column one in the fit); the launch then numbers its
 // waves across the planes.  48x512x512: four two-column strips and 40
-// columns per band, 80.1 -> 71.9 predicted.
+// columns per band, 80.1 -> 71.9 predicted.  They serve every I/O mode: planes
+// with spread columns gain as much (48x512x512 uint8 98.5 -> 71.8 us, float32
+// 217 -> 194; 3x512x512 uint8 15.2 -> 9.8).
 constexpr int kTailStretch = 7;
 
 // spread_bytes: a destination of bytes with spread columns, whose two-column
@@ -382,11 +384,9 @@ void wz_config_for(const weno_tensor_t* src, const weno_tensor_t* dst, int* rows
     *cols = g_cols_per_lane.load();
     *tail_rows = 0;
     const bool share = planes_share_lines(src->c, src->sc, src->sh) || planes_share_lines(dst->c, dst->sc, dst->sh);
-    if (*rows == 0 || *cols == 0) {
+    if (*rows == 0 || *cols == 0)
         wz_auto_config((int64_t)src->n * src->c, src->h, src->w, share, dst->dtype == WENO_U8 && dst->sw != 1, rows,
                        cols, tail_rows);
-        if (dst->sw != 1) *tail_rows = 0;   // tail strips store contiguous columns only
-    }
 }
 
 // the launchers of each I/O mode (weno_zoom.hip)

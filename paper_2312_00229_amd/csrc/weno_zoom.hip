@@ -233,7 +233,7 @@ hipError_t launch_single(const FwdJob& jb, const FwdParams& P, int rows, hipStre
 {
     dim3 grid(wz_grid_x((int64_t)jb.strips_x * jb.strips_y, jb.share), jb.planes);
     if (jb.share) grid = dim3(grid.x * jb.C, jb.planes / jb.C);   // an image's planes interleaved (zoom2x_kernel)
-    if constexpr (COLS == 2 && !io_out_spread(IO)) {
+    if constexpr (COLS == 2) {
         if (jb.tail_rows > 0) {  // one wave index across the planes
             const int64_t waves = (int64_t)jb.planes * ((int64_t)jb.strips_x * jb.strips_y + jb.tail_bands);
             grid = dim3((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock), 1);
