@@ -208,6 +208,19 @@ struct StripLanes {
     int split;               // 1, unknown to the compiler: ends a basic block at every row's stores
 };
 
+// Between a wave's LDS writes and its reads of other lanes' values, and between
+// those reads and the next writes.  The hardware serves a wave's LDS accesses
+// in order, so nothing waits here, but the compiler only keeps the order of
+// accesses that one lane may make to the same address: those of a lane that
+// writes at 4 lane + j and reads at lane + 8 + 64 i never meet, and it may move
+// one past the other.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Buffer resources (gfx9 family descriptor, raw addressing): the plane base
 // and its byte extent sit in SGPRs, the per-lane column offset in a VGPR and
 // the uniform row offset in an SGPR, so loads and stores need no VALU address
@@ -428,8 +441,8 @@ __device__ __forceinline__ void store_quads(const StripCtx& cx, int R, const Str
         // next lane's (48 bytes in HWC RGB): every lane of every store is then
         // an L2 request of its own, 512 per row of quads, and those bind the
         // launch (3x1440x2560 uint8 HWC to float32 HWC: 165 us); in column
-        // order five lanes share one (78 us).  LDS serves a wave's accesses in
-        // order, so no barrier is needed.
+        // order five lanes share one (78 us).  The rows are the wave's own: no
+        // barrier of the block, the order within the wave (wave_lds_order).
         constexpr int N = 2 * COLS, PITCH = kWave * N;
 #pragma unroll
         for (int k = 0; k < COLS; ++k) {
@@ -438,6 +451,7 @@ __device__ __forceinline__ void store_quads(const StripCtx& cx, int R, const Str
             L.stage_wr[PITCH + 2 * k] = c[k];
             L.stage_wr[PITCH + 2 * k + 1] = d[k];
         }
+        wave_lds_order();
         if (L.split) {
 #pragma unroll
             for (int i = 0; i < N; ++i) {
@@ -445,6 +459,7 @@ __device__ __forceinline__ void store_quads(const StripCtx& cx, int R, const Str
                 buf_st_f32(L.stage_rd[PITCH + kWave * i], cx.dst, L.st_out[i], r1);
             }
         }
+        wave_lds_order();
     }
 }
 

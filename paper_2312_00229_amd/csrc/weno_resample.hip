@@ -368,7 +368,8 @@ __global__ __launch_bounds__(256) void cols_pass_kernel(ColPassArgs a, const Sam
 // shrinks (3x4320x7680 -> 3240x5760: 139 us; 97 us with all reads and writes
 // hitting the caches, 120 with the writes alone doing so; 4.5 TB/s against the
 // 5.1 of a plain copy), so nothing may hold a wave up.  The LDS row is the
-// wave's own, and LDS serves a wave in order: there is no barrier.  The wave
+// wave's own: no barrier of the block, the order within the wave
+// (wave_lds_order).  The wave
 // walks the input intervals one by one with kAhead rows requested ahead; the
 // tap rows and the rows in flight are a ring of registers that turns by
 // renaming, eight intervals per trip.  What an interval's taps alone decide
@@ -502,6 +503,7 @@ __global__ __launch_bounds__(kBlock) void wave_resample_kernel(WaveArgs a)
         const InPos p = in_pos(pc.t, pc.k, pc.node);
 #pragma unroll
         for (int m = 0; m < M; ++m) buf[lane + kWave * m] = interval_value<BETA>(I[m], p) * kScale;
+        wave_lds_order();
         const uint32_t so = (uint32_t)r * a.d_h;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -511,6 +513,7 @@ __global__ __launch_bounds__(kBlock) void wave_resample_kernel(WaveArgs a)
             if constexpr (OUT_U8) buf_st_u8(quant_u8(u * 255.0f), dst, vout[q], so);
             else buf_st_f32(u, dst, vout[q], so);
         }
+        wave_lds_order();   // the next row's writes come after these reads
         ++r;
         if (r < r1) pc = position(r);
         if (a.paced) {   // as the doubling's one-round launches (zoom_strip)
