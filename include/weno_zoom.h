@@ -145,7 +145,7 @@ typedef struct {
     int32_t rows_per_strip;  /* launch configuration captured at plan time */
     int32_t cols_per_lane;
     int32_t beta_mode;
-    int64_t reserved;        /* set by the plan */
+    int64_t reserved;        /* set by the plan; a run refuses a plan without it */
 } weno_batch_plan_t;
 
 size_t weno_zoom2x_batched_workspace(int32_t count);

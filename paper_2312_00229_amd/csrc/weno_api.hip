@@ -612,6 +612,7 @@ extern "C" int weno_zoom2x_batched_run(const weno_batch_plan_t* plan, void* hip_
 {
     if (!plan || !plan->d_workspace || plan->count < 1 || plan->total_items < 1) return WENO_EINVAL;
     if (plan->cols_per_lane != 1 && plan->cols_per_lane != 2) return WENO_EINVAL;
+    if (plan->reserved < 1 || plan->reserved >= (1ll << kIoModes)) return WENO_EINVAL;   // the set of modes to launch
     hipStream_t st = (hipStream_t)hip_stream;
     // one launch per I/O mode among the images, nearly always one in all
     for (int io = 0; io < kIoModes; ++io) {
