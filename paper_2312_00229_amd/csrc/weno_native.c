@@ -143,9 +143,10 @@ static PyObject* native_zoom2x(PyObject* self, PyObject* const* a, Py_ssize_t na
     int dev = 0;
     int rc = describe(a[2], &s, &dev);
     if (rc < 0) return NULL;
+    if (rc == 0) Py_RETURN_NONE;   // s is not filled
     PyObject* dtype = a[3] == Py_None ? (s.dtype == WENO_F32 ? g_f32 : g_u8) : a[3];
     // interleaved channels take an output of their own layout
-    if (rc == 0 || (s.sc == 1 && s.c > 1) || (dtype != g_f32 && dtype != g_u8) || s.h > INT32_MAX / 2 ||
+    if ((s.sc == 1 && s.c > 1) || (dtype != g_f32 && dtype != g_u8) || s.h > INT32_MAX / 2 ||
         s.w > INT32_MAX / 2)
         Py_RETURN_NONE;
     PyObject* shape = PyObject_GetAttr(a[2], s_shape);
