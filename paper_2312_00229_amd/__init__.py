@@ -59,10 +59,8 @@ class Params:
     def _build(self) -> WenoParams:
         if self.boundary not in _BOUNDARY:
             raise ValueError("boundary must be 'clamp' or 'external' (got %r)" % (self.boundary,))
-        p = WenoParams(float(self.beta), float(self.k_eps), float(self.h), float(self.nbw),
-                       _BOUNDARY[self.boundary])
-        p.address = ctypes.addressof(p)   # read by the native call path while p is alive
-        return p
+        return WenoParams(float(self.beta), float(self.k_eps), float(self.h), float(self.nbw),
+                          _BOUNDARY[self.boundary])
 
     def c(self) -> WenoParams:
         """The C struct; built once per distinct parameter set."""
@@ -159,7 +157,7 @@ def zoom2x_(x: torch.Tensor, out: torch.Tensor, params: Params | None = None, *,
     """One WD-WENO doubling of x into the caller's `out` (..., 2H, 2W)."""
     p = _params(params, beta, k_eps, h, nbw, boundary)
     if _native is not None:
-        rc = _native.zoom2x_(_lib.lib().address["weno_zoom2x"], p.address, x, out)
+        rc = _native.zoom2x_(_lib.lib().address["weno_zoom2x"], ctypes.addressof(p), x, out)
         if rc is not None:
             if rc != _lib.WENO_OK:
                 _lib.check(rc, "weno_zoom2x")
@@ -180,7 +178,7 @@ def zoom2x(x: torch.Tensor, params: Params | None = None, *, out_dtype=None, bet
     the samples beyond the plane (the paper's function tests pass f there)."""
     if _native is not None:
         p = _params(params, beta, k_eps, h, nbw, boundary)
-        out = _native.zoom2x(_lib.lib().address["weno_zoom2x"], p.address, x, out_dtype)
+        out = _native.zoom2x(_lib.lib().address["weno_zoom2x"], ctypes.addressof(p), x, out_dtype)
         if out is not None:
             if type(out) is int:
                 _lib.check(out, "weno_zoom2x")
@@ -281,7 +279,7 @@ def zoom2x_backward(x: torch.Tensor, grad_y: torch.Tensor, params: Params | None
                                                                                tuple(out.shape)))
         gx = out
     if _native is not None:
-        rc = _native.zoom2x_backward(_lib.lib().address["weno_zoom2x_backward"], p.address, x, grad_y, gx)
+        rc = _native.zoom2x_backward(_lib.lib().address["weno_zoom2x_backward"], ctypes.addressof(p), x, grad_y, gx)
         if rc is not None:
             if rc != _lib.WENO_OK:
                 _lib.check(rc, "weno_zoom2x_backward")
