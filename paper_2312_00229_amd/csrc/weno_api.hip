@@ -490,26 +490,43 @@ static int batched_check(const weno_tensor_t* srcs, const weno_tensor_t* dsts, i
 // (iteration_cost): a compute unit's waves share its strips out one by one, so
 // it takes the rounds of its busiest wave, about 0.4 of a round more than the
 // mean, at the rate of the waves that share a SIMD.  Two-column strips of bytes
-// cost more per iteration than the model's float rows (x 1.17).  Interleaved
-// float rows take short one-column strips: the planes of a strip drift apart
-// as they go down, and with them the parts of the lines that an L2 should put
-// together (256 float32 HWC images of 64 to 512 squared: 16 rows 566 us, 64
-// rows 720, two columns 633 and 796).  On six batches of 8 to 512 images, all
-// types, the pick is within 7 % of the best of 24 shapes (24 uint8 HWC images
-// of 85 to 415 squared 40-45 us, 512 of 32 to 1024 squared 2353; 32-row
-// two-column strips, the choice before, 49 and 2424).
+// cost more per iteration than the model's float rows (x 1.17), as do those of
+// floats from or to interleaved planes.  Interleaved float destinations take
+// short one-column strips: the planes of a strip drift apart as they go down,
+// and with them the parts of the lines that an L2 should put together (256
+// float32 HWC images of 64 to 512 squared: 16 rows 566 us, 64 rows 720, two
+// columns 633 and 796; 512 uint8 HWC to float32 HWC of 32 to 1024 squared 1145
+// and, in 24 rows, 1264).  They decide where they hold an eighth of the pixels
+// (a quarter among uint8 HWC images: 128 images 158 us, in 32 rows 166); one
+// among 511 uint8 HWC images does not (16 rows 873 us, 96 rows 820).
+// A batch with a float destination and an interleaved end takes such strips
+// too while they are no more than six rounds of waves: its planes are walked
+// side by side, and short strips leave fewer waves waiting at the end (uint8
+// HWC to planar float32, 16 rows against the model's: 24 images 37 and 42 us,
+// 64 images 69 and 72, 128 images, 6.5 rounds, 158 and 151, 256 images 267 and
+// 257).  On batches of 8 to
+// 512 images, all types, the pick is within 16 % of the best of 14 shapes, for
+// most within 5 (24 uint8 HWC images of 85 to 415 squared 40-45 us, 512 of 32 to
+// 1024 squared 2353; 32-row two-column strips, the choice before, 49 and 2424).
 static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts, int32_t count, int* rows, int* cols)
 {
     const int64_t cus = wz_device_cus();
-    bool bytes = false, spread = false;
-    int64_t together = 1;   // planes of a strip taken together
+    bool bytes = false, floats_shared = false;
+    int64_t together = 1;              // planes of a strip taken together
+    int64_t px = 0, px_spread = 0;     // pixels: all, and those of interleaved float destinations
+    int64_t short_strips = 0;          // one-column strips of 16 rows
     for (int i = 0; i < count; ++i) {
         const bool share = planes_share_lines(srcs[i].c, srcs[i].sc, srcs[i].sh) ||
                            planes_share_lines(dsts[i].c, dsts[i].sc, dsts[i].sh);
         bytes = bytes || dsts[i].dtype == WENO_U8;
-        spread = spread || (dsts[i].dtype == WENO_F32 && share);
+        floats_shared = floats_shared || (dsts[i].dtype == WENO_F32 && share);
+        const int64_t planes = (int64_t)srcs[i].n * srcs[i].c, image = planes * srcs[i].h * srcs[i].w;
+        px += image;
+        if (dsts[i].dtype == WENO_F32 && planes_share_lines(dsts[i].c, dsts[i].sc, dsts[i].sh)) px_spread += image;
+        short_strips += planes * ((srcs[i].w + strip_own<1>() - 1) / strip_own<1>()) * ((srcs[i].h + 15) / 16);
         if (share) together = std::max<int64_t>(together, srcs[i].c);
     }
+    const bool spread = 8 * px_spread >= px || (floats_shared && short_strips <= 6 * 16 * cus);
     double best = 0.0;
     for (int c = 2; c >= 1; --c) {
         if (spread && c == 2) continue;
@@ -531,7 +548,7 @@ static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts,
             const double rounds = (double)per_cu / (double)std::min(per_cu, 4 * resident);
             double each = longest + kStartCost;
             if (rounds > 1.0) each = std::max(each, (rounds + 0.4) * (double)iterations / (double)strips);
-            const double cost = (double)m * each * iteration_cost(c, m) * (bytes && c == 2 ? 1.17 : 1.0);
+            const double cost = (double)m * each * iteration_cost(c, m) * ((bytes || floats_shared) && c == 2 ? 1.17 : 1.0);
             if (best == 0.0 || cost < best) {
                 best = cost;
                 *rows = r;
