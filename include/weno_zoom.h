@@ -161,7 +161,7 @@ int weno_zoom2x_batched(const weno_tensor_t* srcs, const weno_tensor_t* dsts, in
  * harnesses that forbid hipMalloc): weno_zoom2x_batched without a caller
  * workspace.  The image table lives in a fixed device
  * array inside the library, one per GPU, kept until the process ends
- * (about 700 KB).  The call allocates nothing; like weno_zoom2x_batched it
+ * (about 850 KB).  The call allocates nothing; like weno_zoom2x_batched it
  * copies the table to the device and waits for the stream once before the
  * launch (so it cannot be captured into a graph; use the plan/run pair with a
  * caller workspace for that).

@@ -181,6 +181,18 @@ int wz_source_region(const weno_tensor_t* src, int boundary, weno_tensor_t* regi
     return WENO_OK;
 }
 
+// I/O mode of a doubling.  A lane's outputs are stored together where the
+// columns are contiguous.  Float rows are 4-byte aligned, which is all a vector
+// store needs (a pointer that is not takes element stores); packed bytes go out
+// as one word at any alignment, which this architecture allows buffer stores.
+static int io_mode(const weno_tensor_t* src, const weno_tensor_t* dst)
+{
+    const bool in_u8 = src->dtype == WENO_U8, out_u8 = dst->dtype == WENO_U8;
+    const bool rows_ok = dst->sw == 1 && (out_u8 || (uintptr_t)dst->data % 4 == 0);
+    if (out_u8) return in_u8 ? (rows_ok ? kIoU8 : kIoU8S) : (rows_ok ? kIoF32U8 : kIoF32U8S);
+    return in_u8 ? (rows_ok ? kIoU8F32 : kIoU8F32S) : (rows_ok ? kIoF32 : kIoF32S);
+}
+
 // tail_rows > 0 (two columns only): the last strip column is walked by
 // one-column strips of tail_rows rows (zoom2x_kernel)
 FwdJob wz_make_job(const weno_tensor_t* src, const weno_tensor_t* dst, int cols, int rows_per_strip, int boundary,
@@ -216,13 +228,7 @@ FwdJob wz_make_job(const weno_tensor_t* src, const weno_tensor_t* dst, int cols,
         jb.tail_bands = (src->h + tail_rows - 1) / tail_rows;
     }
     jb.share = planes_share_lines(jb.C, jb.s_c, jb.s_h) || planes_share_lines(jb.C, jb.d_c, jb.d_h);
-    // A lane's outputs are stored together where the columns are contiguous.
-    // Float rows are 4-byte aligned, which is all a vector store needs (a
-    // pointer that is not takes element stores); packed bytes go out as one
-    // word at any alignment, which this architecture allows buffer stores.
-    const bool rows_ok = dst->sw == 1 && (jb.out_u8 || (uintptr_t)dst->data % 4 == 0);
-    if (jb.out_u8) jb.io = jb.in_u8 ? (rows_ok ? kIoU8 : kIoU8S) : (rows_ok ? kIoF32U8 : kIoF32U8S);
-    else jb.io = jb.in_u8 ? (rows_ok ? kIoU8F32 : kIoU8F32S) : (rows_ok ? kIoF32 : kIoF32S);
+    jb.io = io_mode(src, dst);
     jb.dst_extent = (uint32_t)wz_plane_extent(dst);
     weno_tensor_t region;
     wz_source_region(src, boundary, &region);   // validated by the caller
@@ -511,20 +517,17 @@ static int batched_check(const weno_tensor_t* srcs, const weno_tensor_t* dsts, i
 static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts, int32_t count, int* rows, int* cols)
 {
     const int64_t cus = wz_device_cus();
-    bool bytes = false, floats_shared = false;
-    int64_t together = 1;              // planes of a strip taken together
+    bool floats_shared = false;
     int64_t px = 0, px_spread = 0;     // pixels: all, and those of interleaved float destinations
     int64_t short_strips = 0;          // one-column strips of 16 rows
     for (int i = 0; i < count; ++i) {
         const bool share = planes_share_lines(srcs[i].c, srcs[i].sc, srcs[i].sh) ||
                            planes_share_lines(dsts[i].c, dsts[i].sc, dsts[i].sh);
-        bytes = bytes || dsts[i].dtype == WENO_U8;
         floats_shared = floats_shared || (dsts[i].dtype == WENO_F32 && share);
         const int64_t planes = (int64_t)srcs[i].n * srcs[i].c, image = planes * srcs[i].h * srcs[i].w;
         px += image;
         if (dsts[i].dtype == WENO_F32 && planes_share_lines(dsts[i].c, dsts[i].sc, dsts[i].sh)) px_spread += image;
         short_strips += planes * ((srcs[i].w + strip_own<1>() - 1) / strip_own<1>()) * ((srcs[i].h + 15) / 16);
-        if (share) together = std::max<int64_t>(together, srcs[i].c);
     }
     const bool spread = 8 * px_spread >= px || (floats_shared && short_strips <= 6 * 16 * cus);
     double best = 0.0;
@@ -534,21 +537,35 @@ static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts,
         const int64_t resident = c == 1 ? 4 : 3;   // waves per SIMD (zoom2x_batched_kernel)
         for (int r : {8, 16, 24, 32, 48, 64, 96}) {
             if (spread && r > 16) break;
-            int64_t strips = 0, iterations = 0;
-            int longest = 0;
+            struct Launch {
+                int64_t strips, iterations, units[17];   // units by their planes
+                int longest;
+            } launches[kIoModes] = {};
             for (int i = 0; i < count; ++i) {
-                const int64_t walks = (int64_t)srcs[i].n * srcs[i].c * ((srcs[i].w + own - 1) / own);
+                const bool share = planes_share_lines(srcs[i].c, srcs[i].sc, srcs[i].sh) ||
+                                   planes_share_lines(dsts[i].c, dsts[i].sc, dsts[i].sh);
+                Launch& l = launches[io_mode(&srcs[i], &dsts[i])];
+                const int64_t places = (int64_t)srcs[i].n * ((srcs[i].w + own - 1) / own), walks = places * srcs[i].c;
                 const int64_t bands = (srcs[i].h + r - 1) / r;
-                strips += walks * bands;
-                iterations += walks * (srcs[i].h + kStartCost * bands);
-                longest = std::max(longest, (int)((srcs[i].h + bands - 1) / bands));
+                l.strips += walks * bands;
+                l.units[wz_unit_planes(srcs[i].c, share)] +=
+                    places * bands * (share ? wz_unit_groups(srcs[i].c, true) : srcs[i].c);
+                l.iterations += walks * (srcs[i].h + kStartCost * bands);
+                l.longest = std::max(l.longest, (int)((srcs[i].h + bands - 1) / bands));
             }
-            const int64_t per_cu = ((strips + together - 1) / together + cus - 1) / cus * together;
-            const int64_t m = std::min(resident, (per_cu + 3) / 4);   // waves per SIMD
-            const double rounds = (double)per_cu / (double)std::min(per_cu, 4 * resident);
-            double each = longest + kStartCost;
-            if (rounds > 1.0) each = std::max(each, (rounds + 0.4) * (double)iterations / (double)strips);
-            const double cost = (double)m * each * iteration_cost(c, m) * ((bytes || floats_shared) && c == 2 ? 1.17 : 1.0);
+            double cost = 0.0;   // the launches follow each other
+            for (int io = 0; io < kIoModes; ++io) {
+                const Launch& l = launches[io];
+                if (l.strips == 0) continue;
+                int64_t per_cu = 0;   // strips of the busiest compute unit
+                for (int planes = 1; planes <= 16; ++planes) per_cu += (l.units[planes] + cus - 1) / cus * planes;
+                const int64_t m = std::min(resident, (per_cu + 3) / 4);   // waves per SIMD
+                const double rounds = (double)per_cu / (double)std::min(per_cu, 4 * resident);
+                double each = l.longest + kStartCost;
+                if (rounds > 1.0) each = std::max(each, (rounds + 0.4) * (double)l.iterations / (double)l.strips);
+                cost += (double)m * each * iteration_cost(c, m) *
+                        (c == 2 && (io_out_u8(io) || floats_shared) ? 1.17 : 1.0);
+            }
             if (best == 0.0 || cost < best) {
                 best = cost;
                 *rows = r;
@@ -571,7 +588,8 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
     if (rc) return rc;
     int rows = g_rows_per_strip.load(), cols = g_cols_per_lane.load();
     if (rows == 0 || cols == 0) batched_config(srcs, dsts, count, &rows, &cols);
-    // by I/O mode (each has a launch of its own), then largest images first
+    // by I/O mode (each has a launch of its own), then most planes per unit (one
+    // run of units after another, zoom2x_batched_kernel), then largest images first
     std::vector<FwdJob> made(count);
     std::vector<int> order(count);
     for (int i = 0; i < count; ++i) {
@@ -583,32 +601,41 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         const FwdJob &A = made[a], &B = made[b];
         if (A.io != B.io) return A.io < B.io;
+        const int ua = wz_unit_planes(A.C, A.share), ub = wz_unit_planes(B.C, B.share);
+        if (ua != ub) return ua > ub;
         return (int64_t)A.H * A.W * A.planes > (int64_t)B.H * B.W * B.planes;
     });
     std::vector<uint8_t> host(batch_table_bytes(count), 0);
-    BatchTable* tab = (BatchTable*)host.data();
-    FwdJob* jobs = (FwdJob*)(host.data() + batch_jobs_offset());
+    FwdJob* jobs = (FwdJob*)(host.data() + batch_jobs_offset(count));
     int64_t* prefix = (int64_t*)(host.data() + batch_prefix_offset(count));
     FwdParams* prm = (FwdParams*)(host.data() + batch_params_offset(count));
+    BatchRun* runs = (BatchRun*)(host.data() + batch_runs_offset());
     int64_t total = 0, modes = 0, items = 0;
-    int io = 0;   // modes [0, io] have their first unit
+    BatchRun* run = nullptr;   // the run of image k - 1
+    int more = kIoModes;       // entries of runs
     for (int k = 0; k < count; ++k) {
-        jobs[k] = made[order[k]];
-        while (io < jobs[k].io) tab->first[++io] = total;
-        modes |= 1ll << io;
-        prm[k] = wz_fwd_params(p, jobs[k].in_u8, jobs[k].out_u8);
+        const FwdJob& jb = jobs[k] = made[order[k]];
+        prm[k] = wz_fwd_params(p, jb.in_u8, jb.out_u8);
+        const int together = wz_unit_planes(jb.C, jb.share);
+        const bool new_mode = !((modes >> jb.io) & 1);
+        if (new_mode || run->planes != together) {
+            BatchRun* const begun = &runs[new_mode ? jb.io : more];
+            if (!new_mode) run->next = more++;
+            run = begun;
+            run->first = total;
+            run->image = k;
+            run->planes = together;
+            run->next = -1;
+        }
+        modes |= 1ll << jb.io;
         prefix[k] = total;
-        const int64_t strips = (int64_t)jobs[k].planes * jobs[k].strips_x * jobs[k].strips_y;
-        const int together = wz_unit_planes(jobs[k]);
-        tab->slots[io] = std::max(tab->slots[io], together);
-        total += strips / together;
-        items += strips;
+        const int64_t strips = (int64_t)jb.strips_x * jb.strips_y;
+        total += strips * (jb.share ? jb.planes / jb.C * wz_unit_groups(jb.C, true) : jb.planes);
+        items += strips * jb.planes;
+        run->image_end = k + 1;
+        run->end = total;
     }
     prefix[count] = total;
-    while (io < kIoModes) tab->first[++io] = total;
-    tab->count = count;
-    tab->total_items = items;
-    tab->params_offset = batch_params_offset(count);
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e = hipMemcpyAsync(d_workspace, host.data(), host.size(), hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return wz_hip_error(e, "batch table copy");

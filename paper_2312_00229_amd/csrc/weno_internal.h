@@ -10,48 +10,36 @@
 
 // Device-resident table of a batched call, written into the caller's
 // workspace by weno_zoom2x_batched_plan:
-//   [0, 256)                 BatchTable header
-//   [256, ...)               FwdJob jobs[count]       (by I/O mode, then largest image first)
+//   [0, ...)                 BatchRun runs[kIoModes + count]  (the first run of each I/O mode, then the others)
+//   then                     FwdJob jobs[count]       (by I/O mode, then most planes per unit, then
+//                                                     largest image first)
 //   then                     int64_t prefix[count+1]  (first unit of each image: a strip of one plane,
-//                                                     or of all interleaved planes, wz_unit_planes)
+//                                                     or of a group of interleaved planes, wz_unit_planes)
 //   then                     FwdParams params[count]
-struct BatchTable {
-    int64_t first[wz::kIoModes + 1];   // units of mode m: [first[m], first[m + 1])
-    int64_t total_items;
-    int32_t slots[wz::kIoModes];       // tickets per unit of mode m: its largest plane count per unit
-    int32_t count;
-    int32_t pad0;
-    int64_t params_offset;
+// A run: images of one mode with as many planes per unit, units [first, end).
+struct BatchRun {
+    int64_t first, end;
+    int32_t image, image_end;   // its images
+    int32_t planes;             // per unit (tickets)
+    int32_t next;               // the mode's next run, or -1
 };
-
-static_assert(sizeof(BatchTable) <= 256, "the jobs start at byte 256");
-
-__host__ __device__ constexpr size_t batch_jobs_offset() { return 256; }
-__host__ __device__ constexpr size_t batch_prefix_offset(int count)
+constexpr size_t batch_runs_offset() { return 0; }
+constexpr size_t batch_jobs_offset(int count)
 {
-    return batch_jobs_offset() + (size_t)count * sizeof(wz::FwdJob);
+    return batch_runs_offset() + (size_t)(wz::kIoModes + count) * sizeof(BatchRun);
 }
-__host__ __device__ constexpr size_t batch_params_offset(int count)
+constexpr size_t batch_prefix_offset(int count)
+{
+    return batch_jobs_offset(count) + (size_t)count * sizeof(wz::FwdJob);
+}
+constexpr size_t batch_params_offset(int count)
 {
     return (batch_prefix_offset(count) + (size_t)(count + 1) * sizeof(int64_t) + 15) / 16 * 16;
 }
-__host__ __device__ constexpr size_t batch_table_bytes(int count)
+constexpr size_t batch_table_bytes(int count)
 {
     return (batch_params_offset(count) + (size_t)count * sizeof(wz::FwdParams) + 255) / 256 * 256;
 }
-__host__ __device__ inline const wz::FwdJob* batch_jobs(const BatchTable* t)
-{
-    return (const wz::FwdJob*)((const uint8_t*)t + batch_jobs_offset());
-}
-__host__ __device__ inline const int64_t* batch_prefix(const BatchTable* t)
-{
-    return (const int64_t*)((const uint8_t*)t + batch_prefix_offset(t->count));
-}
-__host__ __device__ inline const wz::FwdParams* batch_params(const BatchTable* t)
-{
-    return (const wz::FwdParams*)((const uint8_t*)t + t->params_offset);
-}
-
 // host helpers (weno_api.hip)
 int wz_hip_error(hipError_t e, const char* what);
 int wz_esize(int32_t dtype);
@@ -82,8 +70,17 @@ inline int wz_grid_x(int64_t strips, bool share)
     return (int)(share ? (bx + kXcds - 1) / kXcds * kXcds : bx);
 }
 
-// planes of a unit: the same strip of an image's interleaved planes
-__host__ __device__ inline int wz_unit_planes(const wz::FwdJob& jb) { return jb.share ? jb.C : 1; }
+// Groups of an image's interleaved planes, the same strip of a group being a
+// unit: no more planes than a compute unit has waves for (zoom2x_batched_kernel),
+// so that few strips of many planes still reach many compute units (4 uint8 HWC
+// images of 64 channels and 64 squared 105 -> 33 us).
+__host__ __device__ inline int wz_unit_groups(int C, bool share) { return share ? (C + 15) / 16 : 1; }
+// planes of a unit (the last group may hold fewer)
+__host__ __device__ inline int wz_unit_planes(int C, bool share)
+{
+    const int groups = wz_unit_groups(C, share);
+    return share ? (C + groups - 1) / groups : 1;
+}
 
 // Launches of one I/O mode (weno_zoom.hip, compiled once per mode): one doubling
 // of a job with its beta mode, columns per lane and strip height, and a batch

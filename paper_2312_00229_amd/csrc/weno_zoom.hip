@@ -122,15 +122,21 @@ __global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJo
 
 // Persistent kernel over the strips of many images, those of one I/O mode (a
 // kernel that switched between all modes took the registers of the largest:
-// 176 VGPRs, two waves per SIMD).  A unit is one strip of a plane, or of all
-// the interleaved planes of an image.  One workgroup fills a compute unit (three
-// waves per SIMD, four with one column per lane); workgroup g takes units g,
-// g + grid, ..., and its waves share them out through a ticket in LDS, a ticket
-// being a plane of a unit (`slots` per unit, the largest plane count of the
-// mode's units; a smaller unit's spare tickets are empty).  The planes of a
-// strip, which fill the same lines with a byte in three each, then run side by
-// side on one compute unit, and the lines leave its L2 whole.  The work is
-// vector issue, the same on every compute unit, and the images are stored
+// 176 VGPRs, two waves per SIMD).  A unit is one strip of a plane, or of a group
+// of an image's interleaved planes (wz_unit_groups).  One workgroup fills a
+// compute unit (three waves per SIMD, four with one column per lane); workgroup
+// g takes units g, g + grid, ..., and its waves share them out through a ticket
+// in LDS, a ticket being a plane of a unit.  The table holds the images by their
+// planes per unit, so the units come in runs of equal ticket counts, and a wave
+// goes from run to run as its tickets pass their ends (with the largest count
+// for all, a 64-channel image left 61 empty tickets in each unit of the others:
+// one beside 64 planar float32 images 281 us, now 95).  The planes of a strip,
+// which fill the same lines with a byte in three each, then run side by side on
+// one compute unit, and the lines leave its L2 whole.  Units of more than eight
+// planes, whose images may be in several groups, are dealt out so that every XCD
+// gets consecutive ones: the groups of a strip then meet in one L2 (32 float32
+// HWC images of 64 channels and 64 squared 545 -> 285 us; units of 3 planes
+// would lose, 83 -> 103).  The work is vector issue, the same on every compute unit, and the images are stored
 // largest first and in bands of nearly equal height, so fixed shares come out
 // even; within a compute unit they would not (a SIMD serves its oldest wave
 // first: workgroups of four waves with a ticket each, 2663 us for the 512
@@ -141,46 +147,87 @@ __global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJo
 template <int COLS>
 constexpr int batch_waves() { return COLS == 2 ? 12 : 16; }
 
+// The table's parts come as arguments: read from its header, their addresses
+// would be one more load, from cold memory, ahead of the first strip.
 template <int COLS, int BETA, int IO>
-__global__ __launch_bounds__(kWave * batch_waves<COLS>()) void zoom2x_batched_kernel(const BatchTable* __restrict__ tab)
+__global__ __launch_bounds__(kWave * batch_waves<COLS>()) void zoom2x_batched_kernel(
+    const BatchRun* __restrict__ runs, const FwdJob* __restrict__ jobs, const int64_t* __restrict__ prefix,
+    const FwdParams* __restrict__ params)
 {
     __shared__ int next;
     const int lane = threadIdx.x & (kWave - 1);
-    const int count = tab->count, slots = tab->slots[IO];
-    const int64_t first = tab->first[IO], last = tab->first[IO + 1];   // this mode's units
-    const FwdJob* __restrict__ jobs = batch_jobs(tab);
-    const int64_t* __restrict__ prefix = batch_prefix(tab);
     float* const stage = wave_stage<COLS, IO, batch_waves<COLS>()>();
-    if (threadIdx.x == 0) next = 0;
+    if (threadIdx.x == 0) next = batch_waves<COLS>();
     __syncthreads();
-    for (;;) {
+    auto draw = [&]() {
         int got = 0;
         if (lane == 0) got = atomicAdd(&next, 1);
         // broadcast lane 0's ticket as a provably uniform (scalar) value, so the
         // image table is read with scalar loads and the buffer resources stay
         // in SGPRs
-        const int ticket = __builtin_amdgcn_readfirstlane(got);
-        const int turn = ticket / slots, slot = ticket - turn * slots;
-        const int64_t unit = first + blockIdx.x + (int64_t)turn * gridDim.x;
-        if (unit >= last) break;  // every wave reaches this exit
-        // image k with prefix[k] <= unit < prefix[k+1]
-        int lo = 0, hi = count - 1;
+        return __builtin_amdgcn_readfirstlane(got);
+    };
+    // the workgroup's place among the units of a run
+    auto place = [&](int planes) {
+        const int nb = gridDim.x, xcd = blockIdx.x % kXcds;
+        return planes > 8 ? xcd * (nb / kXcds) + min(xcd, nb % kXcds) + (int)blockIdx.x / kXcds : (int)blockIdx.x;
+    };
+    // The run of units the wave is at, the workgroup's tickets before it, where
+    // the run starts among the places (modulo the grid), and how far ahead of
+    // that the workgroup's first unit is.  The run is read again for every
+    // ticket: kept, it costs the scalar registers of the strip walk.
+    int at = IO, passed = 0, start = 0;
+    // A wave's first ticket is its number, which spreads the first strips over
+    // the SIMDs: drawn, several may go to one (8 gray and RGB uint8 images of 32
+    // to 128 squared 13.1 us, drawn 18.5; 8 float32 HWC ones of 128 to 512
+    // squared in 32-row two-column strips 33, drawn 49).
+    int ticket = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    BatchRun run = runs[at];
+    int ahead = place(run.planes);
+    for (;; run = runs[at], ticket = draw()) {
+        int slot;
+        int64_t unit;
+        for (;;) {
+            const int turn = (ticket - passed) / run.planes;
+            slot = ticket - passed - turn * run.planes;
+            unit = run.first + ahead + (int64_t)turn * gridDim.x;
+            if (unit < run.end) break;
+            if (run.next < 0) return;  // every wave reaches this exit; no barrier follows
+            const int64_t units = run.end - run.first;
+            if (ahead < units) passed += (int)((units - ahead + gridDim.x - 1) / gridDim.x) * run.planes;
+            start = (int)((start + units) % gridDim.x);
+            at = run.next;
+            run = runs[at];
+            ahead = place(run.planes) - start;
+            if (ahead < 0) ahead += (int)gridDim.x;
+        }
+        // image k of the run with prefix[k] <= unit < prefix[k+1]
+        int lo = run.image, hi = run.image_end - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (prefix[mid] <= unit) lo = mid; else hi = mid - 1;
         }
         const FwdJob jb = jobs[lo];
-        const int together = wz_unit_planes(jb);
-        if (slot >= together) continue;
-        const int64_t local = unit - prefix[lo];
+        const FwdParams P = params[lo];
         const int per_plane = jb.strips_x * jb.strips_y;
-        const int group = (int)(local / per_plane);
-        const int wv = (int)(local - (int64_t)group * per_plane);
-        const int plane = group * together + slot;
+        int64_t strip = unit - prefix[lo];   // of the image's planes, or of its interleaved ones as a whole
+        int group = 0;
+        const int groups = wz_unit_groups(jb.C, jb.share);
+        if (groups > 1) {
+            const int64_t whole = strip / groups;
+            group = (int)(strip - whole * groups);
+            strip = whole;
+        }
+        const int outer = (int)(strip / per_plane);
+        const int wv = (int)(strip - (int64_t)outer * per_plane);
         const int sy = wv / jb.strips_x;
         const int sx = wv - sy * jb.strips_x;
-        const int n = plane / jb.C, c = plane - n * jb.C;
-        const FwdParams P = batch_params(tab)[lo];
+        int n = outer, c = group * run.planes + slot;
+        if (!jb.share) {
+            n = outer / jb.C;
+            c = outer - n * jb.C;
+        }
+        if (c >= jb.C) continue;   // the last group holds fewer planes
         const StripCtx cx = make_ctx(jb, n, c, P.out_scale);
         const int R0 = sy * jb.rows;
         const int R1 = min(R0 + jb.rows, jb.H);
@@ -249,8 +296,12 @@ template <int COLS, int BETA, int IO>
 hipError_t launch_batched(const weno_batch_plan_t* plan, hipStream_t st)
 {
     const int64_t blocks = std::min<int64_t>(wz_device_cus(), plan->total_items);
+    const uint8_t* const tab = (const uint8_t*)plan->d_workspace;
     hipLaunchKernelGGL((zoom2x_batched_kernel<COLS, BETA, IO>), dim3((unsigned)blocks),
-                       dim3(kWave * batch_waves<COLS>()), 0, st, (const BatchTable*)plan->d_workspace);
+                       dim3(kWave * batch_waves<COLS>()), 0, st, (const BatchRun*)(tab + batch_runs_offset()),
+                       (const FwdJob*)(tab + batch_jobs_offset(plan->count)),
+                       (const int64_t*)(tab + batch_prefix_offset(plan->count)),
+                       (const FwdParams*)(tab + batch_params_offset(plan->count)));
     return hipGetLastError();
 }
 

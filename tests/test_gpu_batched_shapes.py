@@ -29,6 +29,7 @@ def _dest(interleaved, h, w):
     ([(False, True, 1000)] * 12 + [(False, False, 1000)] * 12, True),
 ])
 def test_shape_of_float_batches(gpu, images, short):
+    gpu.set_launch_config(0, 0)
     xs = [_image(s, h, 1000, torch.uint8, i) for i, (s, _, h) in enumerate(images)]
     outs = [_dest(d, h, 1000) for _, d, h in images]
     plan = gpu.BatchedZoom(xs, outs)

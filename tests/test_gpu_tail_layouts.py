@@ -37,6 +37,7 @@ def _zoom(x, dst, dtype, n, h, w, sc, sh, sw):
 @pytest.mark.parametrize("u8_in", [False, True])
 @pytest.mark.parametrize("n,h,w", SHAPES)
 def test_tails_in_every_layout(gpu, n, h, w, u8_in):
+    gpu.set_launch_config(0, 0)
     gen = torch.Generator(device="cuda").manual_seed(w)
     x = torch.rand((n, h, w), device="cuda", generator=gen)
     if u8_in:
