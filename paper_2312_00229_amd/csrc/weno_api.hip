@@ -492,6 +492,37 @@ static int batched_check(const weno_tensor_t* srcs, const weno_tensor_t* dsts, i
     return WENO_OK;
 }
 
+// waves of 16-row one-column strips that six rounds of a batched launch hold
+static int64_t batched_six_rounds() { return 6 * 16 * (int64_t)wz_device_cus(); }
+static int64_t short_strips(const weno_tensor_t* t)
+{
+    return (int64_t)t->n * t->c * ((t->w + strip_own<1>() - 1) / strip_own<1>()) * ((t->h + 15) / 16);
+}
+
+// I/O modes of a batch's images.  Each mode is a launch, and the launches follow
+// each other, each with its own start and its last waves running alone.  Where
+// images of one pair of types go to contiguous and to spread columns, all take
+// the spread mode, which stores any columns: half planar, half HWC, uint8, 8
+// images of 128 to 512 squared 23.2 -> 17.2 us, 128 of 64 to 512 squared 160 ->
+// 146, 64 of 256 to 1024 squared 381 -> 360; images of all eight modes, 8 57 ->
+// 39, 64 135 -> 107.  Float rows lose more by it, and do so up to six rounds of
+// waves only: 24 images of 85 to 415 squared 47 -> 39, 128 images (6.5 rounds)
+// 190 -> 185, 64 of 256 to 1024 squared (17 rounds) 484 -> 503.
+static std::vector<int> batched_modes(const weno_tensor_t* srcs, const weno_tensor_t* dsts, int32_t count)
+{
+    std::vector<int> io(count);
+    bool present[kIoModes] = {};
+    int64_t strips[kIoModes] = {};   // of both modes of a pair of types, at its contiguous one
+    for (int i = 0; i < count; ++i) {
+        io[i] = io_mode(&srcs[i], &dsts[i]);
+        present[io[i]] = true;
+        strips[io[i] & ~2] += short_strips(&srcs[i]);
+    }
+    for (int& m : io)
+        if (present[m | 2] && (io_out_u8(m) || strips[m & ~2] <= batched_six_rounds())) m |= 2;
+    return io;
+}
+
 // Strip shape of a batch from the cost model of a single launch
 // (iteration_cost): a compute unit's waves share its strips out one by one, so
 // it takes the rounds of its busiest wave, about 0.4 of a round more than the
@@ -514,12 +545,13 @@ static int batched_check(const weno_tensor_t* srcs, const weno_tensor_t* dsts, i
 // 512 images, all types, the pick is within 16 % of the best of 14 shapes, for
 // most within 5 (24 uint8 HWC images of 85 to 415 squared 40-45 us, 512 of 32 to
 // 1024 squared 2353; 32-row two-column strips, the choice before, 49 and 2424).
-static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts, int32_t count, int* rows, int* cols)
+static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts, const std::vector<int>& modes,
+                           int32_t count, int* rows, int* cols)
 {
     const int64_t cus = wz_device_cus();
     bool floats_shared = false;
     int64_t px = 0, px_spread = 0;     // pixels: all, and those of interleaved float destinations
-    int64_t short_strips = 0;          // one-column strips of 16 rows
+    int64_t strips16 = 0;
     for (int i = 0; i < count; ++i) {
         const bool share = planes_share_lines(srcs[i].c, srcs[i].sc, srcs[i].sh) ||
                            planes_share_lines(dsts[i].c, dsts[i].sc, dsts[i].sh);
@@ -527,9 +559,9 @@ static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts,
         const int64_t planes = (int64_t)srcs[i].n * srcs[i].c, image = planes * srcs[i].h * srcs[i].w;
         px += image;
         if (dsts[i].dtype == WENO_F32 && planes_share_lines(dsts[i].c, dsts[i].sc, dsts[i].sh)) px_spread += image;
-        short_strips += planes * ((srcs[i].w + strip_own<1>() - 1) / strip_own<1>()) * ((srcs[i].h + 15) / 16);
+        strips16 += short_strips(&srcs[i]);
     }
-    const bool spread = 8 * px_spread >= px || (floats_shared && short_strips <= 6 * 16 * cus);
+    const bool spread = 8 * px_spread >= px || (floats_shared && strips16 <= batched_six_rounds());
     double best = 0.0;
     for (int c = 2; c >= 1; --c) {
         if (spread && c == 2) continue;
@@ -544,7 +576,7 @@ static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts,
             for (int i = 0; i < count; ++i) {
                 const bool share = planes_share_lines(srcs[i].c, srcs[i].sc, srcs[i].sh) ||
                                    planes_share_lines(dsts[i].c, dsts[i].sc, dsts[i].sh);
-                Launch& l = launches[io_mode(&srcs[i], &dsts[i])];
+                Launch& l = launches[modes[i]];
                 const int64_t places = (int64_t)srcs[i].n * ((srcs[i].w + own - 1) / own), walks = places * srcs[i].c;
                 const int64_t bands = (srcs[i].h + r - 1) / r;
                 l.strips += walks * bands;
@@ -587,7 +619,8 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
     rc = batched_check(srcs, dsts, count, p);
     if (rc) return rc;
     int rows = g_rows_per_strip.load(), cols = g_cols_per_lane.load();
-    if (rows == 0 || cols == 0) batched_config(srcs, dsts, count, &rows, &cols);
+    const std::vector<int> modes_of = batched_modes(srcs, dsts, count);
+    if (rows == 0 || cols == 0) batched_config(srcs, dsts, modes_of, count, &rows, &cols);
     // by I/O mode (each has a launch of its own), then most planes per unit (one
     // run of units after another, zoom2x_batched_kernel), then largest images first
     std::vector<FwdJob> made(count);
@@ -596,6 +629,7 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
         // bands of nearly equal height, `rows` at most
         const int bands = (srcs[i].h + rows - 1) / rows;
         made[i] = wz_make_job(&srcs[i], &dsts[i], cols, (srcs[i].h + bands - 1) / bands, p->boundary, 0);
+        made[i].io = modes_of[i];
         order[i] = i;
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
@@ -658,7 +692,7 @@ extern "C" int weno_zoom2x_batched_run(const weno_batch_plan_t* plan, void* hip_
     if (plan->cols_per_lane != 1 && plan->cols_per_lane != 2) return WENO_EINVAL;
     if (plan->reserved < 1 || plan->reserved >= (1ll << kIoModes)) return WENO_EINVAL;   // the set of modes to launch
     hipStream_t st = (hipStream_t)hip_stream;
-    // one launch per I/O mode among the images, nearly always one in all
+    // one launch per I/O mode of the plan, nearly always one in all
     for (int io = 0; io < kIoModes; ++io) {
         if (!((plan->reserved >> io) & 1)) continue;
         const hipError_t e = kZoomLaunchers[io].batched(plan, st);
