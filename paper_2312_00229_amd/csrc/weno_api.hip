@@ -393,6 +393,13 @@ void wz_config_for(const weno_tensor_t* src, const weno_tensor_t* dst, int* rows
     if (*rows == 0 || *cols == 0)
         wz_auto_config((int64_t)src->n * src->c, src->h, src->w, share, dst->dtype == WENO_U8 && dst->sw != 1, rows,
                        cols, tail_rows);
+    // taller strips where a set height would need more workgroups than a launch
+    // may have (a column of 2^29 samples in 4-row strips: 2^25)
+    const int own = *cols == 1 ? strip_own<1>() : strip_own<2>();
+    const int64_t strips_x = (src->w + own - 1) / own;
+    while (*tail_rows == 0 && *rows < 4096 &&
+           wz_grid_blocks(strips_x * ((src->h + *rows - 1) / *rows), share) * (share ? src->c : 1) > kMaxGridX)
+        *rows *= 2;
 }
 
 // the launchers of each I/O mode (weno_zoom.hip)

@@ -60,15 +60,20 @@ inline bool planes_share_lines(int C, int64_t sc, int64_t sh)
     return C > 1 && sc < sh   /* strides are never negative */;
 }
 
+// Workgroups along x that a launch may have: the work-items of a dimension are
+// counted in 32 bits, and a launch of more runs without the rest, with no error.
+constexpr int64_t kMaxGridX = (1ll << 32) / wz::kBlock - 1;
+
 // Workgroups of a plane of `strips` strips: padded to a multiple of the XCD
 // count when the planes share lines (zoom2x_kernel), the padding exiting at
 // once.  The busiest XCD then holds planes x grid_x / 8 of them.
-inline int wz_grid_x(int64_t strips, bool share)
+inline int64_t wz_grid_blocks(int64_t strips, bool share)
 {
     using namespace wz;
     const int64_t bx = (strips + kWavesPerBlock - 1) / kWavesPerBlock;
-    return (int)(share ? (bx + kXcds - 1) / kXcds * kXcds : bx);
+    return share ? (bx + kXcds - 1) / kXcds * kXcds : bx;
 }
+inline int wz_grid_x(int64_t strips, bool share) { return (int)wz_grid_blocks(strips, share); }
 
 // Groups of an image's interleaved planes, the same strip of a group being a
 // unit: no more planes than a compute unit has waves for (zoom2x_batched_kernel),

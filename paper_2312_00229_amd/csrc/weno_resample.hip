@@ -961,9 +961,14 @@ int launch_wave(const weno_tensor_t* src, const weno_tensor_t* dst, WaveShape fs
     a.eps4_in = eps4_of(p, h, in_u8);
     a.eps4 = eps4_of(p, h, false);
     a.beta = p->beta;
-    const int64_t waves = (int64_t)((dst->h + a.run - 1) / a.run) * fs.ctiles;
-    int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (a.share) blocks = (blocks + kXcds - 1) / kXcds * kXcds * a.C;
+    auto grid_x = [&]() {
+        const int64_t waves = (int64_t)((dst->h + a.run - 1) / a.run) * fs.ctiles;
+        const int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
+        return a.share ? (blocks + kXcds - 1) / kXcds * kXcds * a.C : blocks;
+    };
+    // a column or two of a billion rows: the longest runs fit any plane
+    if (grid_x() > kMaxGridX) a.run = kMaxRun;
+    const int64_t blocks = grid_x();
     const dim3 grid((unsigned)blocks, (unsigned)(a.share ? a.planes / a.C : a.planes));
     if (p->beta == 2.0f) launch_wave_beta<2>(a, fs.m, in_u8, out_u8, grid, st);
     else launch_wave_beta<kBetaGeneral>(a, fs.m, in_u8, out_u8, grid, st);
