@@ -320,9 +320,15 @@ constexpr int kStartCost = 4;
 constexpr int kTailStretch = 7;
 
 // spread_bytes: a destination of bytes with spread columns, whose two-column
-// kernels store eight elements a row: an iteration costs ~1.09 of the table's
-// (3x1024x1024 float32 to uint8 HWC: 20-row one-column strips 23.4 us, 14-row
-// two-column ones, the pick without the factor, 24.0).
+// kernels store eight elements a row: an iteration costs ~1.09 of the table's,
+// with tail strips too.  On 18 shapes from 3x64x64 to 3x4320x7680 to uint8 HWC
+// and to every second column, the pick with the factor is never slower than
+// without and up to 18 % faster (4x700x1000 float32 to uint8 HWC 21.5 us against
+// 26.0, 3x768x1024 18.5 and 20.8, 3x1500x954 30.1 and 32.8); on 43 shapes whose
+// pick it changes from tail strips, 14 % faster to 5 % slower, 4 % faster on
+// average (4x480x640 12.6 and 14.2, 48x600x591 107 and 102).  Rows of packed
+// bytes cost what the table says; a batch's unpaced strips cost more
+// (batched_config).
 void wz_auto_config(int64_t planes, int H, int W, bool share, bool spread_bytes, int* rows, int* cols, int* tail_rows)
 {
     const int64_t cus = wz_device_cus();
@@ -368,7 +374,7 @@ void wz_auto_config(int64_t planes, int H, int W, bool share, bool spread_bytes,
             const int64_t waves = planes * (s2 * ((H + r - 1) / r) + (H + rt - 1) / rt);
             const int64_t blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
             const int64_t mm = (blocks + cus - 1) / cus;
-            const double cost = (double)mm * (r + kStartCost) * iteration_cost(2, mm);
+            const double cost = (double)mm * (r + kStartCost) * iteration_cost(2, mm) * (spread_bytes ? 1.09 : 1.0);
             if (cost < best) {
                 best = cost;
                 best_rows = r;
