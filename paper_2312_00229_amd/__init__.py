@@ -140,10 +140,24 @@ def _c_params(beta, k_eps, h, nbw, boundary) -> WenoParams:
     return Params(beta=beta, k_eps=k_eps, h=h, nbw=nbw, boundary=boundary)._build()
 
 
+@functools.lru_cache(maxsize=64)
+def _c_params_at(beta, k_eps, h, nbw, boundary):
+    p = _c_params(beta, k_eps, h, nbw, boundary)
+    return p, ctypes.addressof(p)
+
+
 def _params(params, beta, k_eps, h, nbw, boundary="clamp") -> WenoParams:
     if params is None:
         return _c_params(beta, k_eps, h, nbw, boundary)
     return params.c()
+
+
+def _params_at(params, beta, k_eps, h, nbw, boundary):
+    """The C struct of a call's parameters and its address, valid while the struct is held."""
+    if params is None:
+        return _c_params_at(beta, k_eps, h, nbw, boundary)
+    p = _params(params, beta, k_eps, h, nbw, boundary)
+    return p, ctypes.addressof(p)
 
 
 def _empty_like_layout(x: torch.Tensor, scale: int, dtype) -> torch.Tensor:
@@ -155,9 +169,9 @@ def _empty_like_layout(x: torch.Tensor, scale: int, dtype) -> torch.Tensor:
 def zoom2x_(x: torch.Tensor, out: torch.Tensor, params: Params | None = None, *, beta=2.0, k_eps=1e-8,
             h=1.0, nbw=-1.0, boundary="clamp") -> torch.Tensor:
     """One WD-WENO doubling of x into the caller's `out` (..., 2H, 2W)."""
-    p = _params(params, beta, k_eps, h, nbw, boundary)
+    p, at = _params_at(params, beta, k_eps, h, nbw, boundary)
     if _native is not None:
-        rc = _native.zoom2x_(_lib.lib().address["weno_zoom2x"], ctypes.addressof(p), x, out)
+        rc = _native.zoom2x_(_lib.lib().address["weno_zoom2x"], at, x, out)
         if rc is not None:
             if rc != _lib.WENO_OK:
                 _lib.check(rc, "weno_zoom2x")
@@ -177,8 +191,8 @@ def zoom2x(x: torch.Tensor, params: Params | None = None, *, out_dtype=None, bet
     view into a larger array and its 4 rows/columns before and 5 after are
     the samples beyond the plane (the paper's function tests pass f there)."""
     if _native is not None:
-        p = _params(params, beta, k_eps, h, nbw, boundary)
-        out = _native.zoom2x(_lib.lib().address["weno_zoom2x"], ctypes.addressof(p), x, out_dtype)
+        p, at = _params_at(params, beta, k_eps, h, nbw, boundary)
+        out = _native.zoom2x(_lib.lib().address["weno_zoom2x"], at, x, out_dtype)
         if out is not None:
             if type(out) is int:
                 _lib.check(out, "weno_zoom2x")

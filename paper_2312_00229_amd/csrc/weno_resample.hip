@@ -1075,8 +1075,7 @@ int launch_block(const weno_tensor_t* src, const weno_tensor_t* dst, const Block
     return e == hipSuccess ? WENO_OK : wz_hip_error(e, "block_resample_kernel launch");
 }
 
-// row pitch (floats) of workspace planes: a multiple of 4, so that rows are
-// 16-byte aligned and the forward kernel stores them with vector stores
+// row pitch (floats) of workspace planes: a multiple of 4 (cascade_pitch)
 int64_t f32_pitch(int64_t w) { return (w + 3) / 4 * 4; }
 
 weno_tensor_t planar_f32(void* data, int n, int c, int h, int w)
