@@ -784,13 +784,15 @@ __device__ __forceinline__ void zoom_strip(const StripCtx& cx, const FwdParams& 
                 strip_step<COLS, BETA, IO, 0, ST>(s, QA, cx, P, L, r + k + 1);
             }
         };
-        // Long float launches enter the loop after a trip peeled off it: the
-        // memory operations before the first loop trip are then those of
-        // every trip, and the compiler's wait counts exact rather than those
-        // of the store-free prologue (3x4320x7680: 0.513 -> 0.510 ms).  Paced
-        // launches and bytes take the code of half the size (the 256^2 cascade
-        // 39.5 -> 39.1 us, 512 uint8 images 2534 -> 2526 us).
-        if constexpr (!PACED && !io_out_u8(IO)) {
+        // Long float launches, and paced one-column byte launches, enter the loop
+        // after a trip peeled off it: the memory operations before the first loop trip
+        // are then those of every trip, and the compiler's wait counts exact
+        // rather than those of the store-free prologue (3x4320x7680: 0.513 ->
+        // 0.510 ms; uint8 3x333x444 7.2 -> 7.0 us, 3x2097x102 8.75 -> 8.65).
+        // Paced floats, two-column bytes and batches of bytes take the code of half
+        // the size (the 256^2 cascade 37.6 -> 37.1 us, 512 uint8 images 2415 ->
+        // 2409).
+        if constexpr (io_out_u8(IO) ? COLS == 1 && PACED : !PACED) {
             if (R + TRIP - 1 < R1) {
                 trip(R);
                 R += TRIP;
