@@ -174,17 +174,16 @@ __global__ __launch_bounds__(kWave * batch_waves<COLS>()) void zoom2x_batched_ke
     };
     // The run of units the wave is at, the workgroup's tickets before it, where
     // the run starts among the places (modulo the grid), and how far ahead of
-    // that the workgroup's first unit is.  The run is read again for every
-    // ticket: kept, it costs the scalar registers of the strip walk.
-    int at = IO, passed = 0, start = 0;
+    // that the workgroup's first unit is
+    int passed = 0, start = 0;
     // A wave's first ticket is its number, which spreads the first strips over
     // the SIMDs: drawn, several may go to one (8 gray and RGB uint8 images of 32
     // to 128 squared 13.1 us, drawn 18.5; 8 float32 HWC ones of 128 to 512
     // squared in 32-row two-column strips 33, drawn 49).
     int ticket = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    BatchRun run = runs[at];
+    BatchRun run = runs[IO];
     int ahead = place(run.planes);
-    for (;; run = runs[at], ticket = draw()) {
+    for (;; ticket = draw()) {
         int slot;
         int64_t unit;
         for (;;) {
@@ -196,8 +195,7 @@ __global__ __launch_bounds__(kWave * batch_waves<COLS>()) void zoom2x_batched_ke
             const int64_t units = run.end - run.first;
             if (ahead < units) passed += (int)((units - ahead + gridDim.x - 1) / gridDim.x) * run.planes;
             start = (int)((start + units) % gridDim.x);
-            at = run.next;
-            run = runs[at];
+            run = runs[run.next];
             ahead = place(run.planes) - start;
             if (ahead < 0) ahead += (int)gridDim.x;
         }
