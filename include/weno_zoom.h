@@ -117,9 +117,10 @@ int weno_zoom2x(const weno_tensor_t* src, const weno_tensor_t* dst, const weno_p
 
 /*
  * Many independent images of uneven sizes in ONE persistent launch (one per
- * combination of types and destination layout among them): a workgroup per
- * compute unit, whose waves share out every grid-th row strip of the images
- * (ordered largest first).  The outputs are bit-identical to weno_zoom2x
+ * combination of types among them, and one more where large float batches mix
+ * contiguous and spread destination columns): a workgroup per compute unit, whose
+ * waves share out every grid-th row strip of the images (ordered largest
+ * first).  The outputs are bit-identical to weno_zoom2x
  * called per image with the same launch configuration.
  *
  * Two steps, so that the launch itself can be captured into a hipGraph:
@@ -134,8 +135,9 @@ int weno_zoom2x(const weno_tensor_t* src, const weno_tensor_t* dst, const weno_p
  *                     overlap any input or another output.
  *   d_workspace:      DEVICE memory, 256-byte aligned, at least
  *                     weno_zoom2x_batched_workspace(count) bytes, owned by the
- *                     caller and left untouched between plan and run.  Runs
- *                     that share a workspace must be ordered on one stream.
+ *                     caller and left untouched between plan and run.  A run
+ *                     only reads it; plans and runs that share a workspace
+ *                     must be ordered, as a plan writes it.
  */
 typedef struct {
     void* d_workspace;
@@ -250,8 +252,10 @@ int weno_zoom2x_backward(const weno_tensor_t* x, const weno_tensor_t* grad_y, co
  * two-column strips and 40 columns), the automatic choice may walk that
  * column in one-column strips of taller bands ("tail" strips).  The
  * configuration changes speed only: every configuration produces
- * bit-identical outputs.  Batched plans capture the configuration when they
- * are made (automatic: 32 rows, 2 columns, no tail strips).
+ * bit-identical outputs.  Strips so short that a launch of them would pass
+ * 2^32 work-items (a column of 2^28 rows or more) are made taller.  Batched plans
+ * capture the configuration when they are made (automatic: the strip height and
+ * columns per lane that the same model gives the whole batch, no tail strips).
  * weno_get_launch_config reports (0, 0) in automatic mode.
  * Returns WENO_EINVAL for values outside these sets.
  */

@@ -659,6 +659,7 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
     FwdParams* prm = (FwdParams*)(host.data() + batch_params_offset(count));
     BatchRun* runs = (BatchRun*)(host.data() + batch_runs_offset());
     int64_t total = 0, modes = 0, items = 0;
+    for (int io = 0; io < kIoModes; ++io) runs[io] = {0, 0, 0, 0, 1, -1};   // modes without images: empty runs
     BatchRun* run = nullptr;   // the run of image k - 1
     int more = kIoModes;       // entries of runs
     for (int k = 0; k < count; ++k) {

@@ -40,6 +40,7 @@ constexpr size_t batch_table_bytes(int count)
 {
     return (batch_params_offset(count) + (size_t)count * sizeof(wz::FwdParams) + 255) / 256 * 256;
 }
+
 // host helpers (weno_api.hip)
 int wz_hip_error(hipError_t e, const char* what);
 int wz_esize(int32_t dtype);

@@ -136,19 +136,19 @@ __global__ __launch_bounds__(kBlock, COLS == 2 ? 3 : 1) void zoom2x_kernel(FwdJo
 // planes, whose images may be in several groups, are dealt out so that every XCD
 // gets consecutive ones: the groups of a strip then meet in one L2 (32 float32
 // HWC images of 64 channels and 64 squared 545 -> 285 us; units of 3 planes
-// would lose, 83 -> 103).  The work is vector issue, the same on every compute unit, and the images are stored
-// largest first and in bands of nearly equal height, so fixed shares come out
-// even; within a compute unit they would not (a SIMD serves its oldest wave
-// first: workgroups of four waves with a ticket each, 2663 us for the 512
-// images below).  A queue for the whole device does not pay: a ticket drawn by
-// atomics on one address takes ~14 ns, one after another, and each wave's
+// would lose, 83 -> 103).  The work is vector issue, the same on every compute
+// unit, and the images are stored largest first and in bands of nearly equal
+// height, so fixed shares come out even; within a compute unit they would not (a
+// SIMD serves its oldest wave first: workgroups of four waves with a ticket each,
+// 2663 us for the 512 images below).  A queue for the whole device does not pay:
+// a ticket drawn by atomics on one address takes ~14 ns, one after another, and each wave's
 // last, empty one too (24 uint8 HWC images of 85 to 415 squared 82 -> 49 us
 // in the same strips, 512 of 32 to 1024 squared 2540 -> 2424).
 template <int COLS>
 constexpr int batch_waves() { return COLS == 2 ? 12 : 16; }
 
-// The table's parts come as arguments: read from its header, their addresses
-// would be one more load, from cold memory, ahead of the first strip.
+// The table's parts come as arguments: an image count read from the table to
+// find them would be one more load, from cold memory, ahead of the first strip.
 template <int COLS, int BETA, int IO>
 __global__ __launch_bounds__(kWave * batch_waves<COLS>()) void zoom2x_batched_kernel(
     const BatchRun* __restrict__ runs, const FwdJob* __restrict__ jobs, const int64_t* __restrict__ prefix,
