@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -621,9 +622,20 @@ static void batched_config(const weno_tensor_t* srcs, const weno_tensor_t* dsts,
     }
 }
 
-extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_tensor_t* dsts, int32_t count,
-                                        const weno_params_t* p, void* d_workspace, size_t ws_bytes,
-                                        void* hip_stream, weno_batch_plan_t* plan)
+// Host memory that runs out while a plan is made is an error of the call: no
+// exception leaves a C entry.
+template <typename F>
+static int guarded(F&& call)
+{
+    try {
+        return call();
+    } catch (const std::bad_alloc&) {
+        return wz_hip_error(hipErrorOutOfMemory, "host memory of a batch plan");
+    }
+}
+
+static int make_plan(const weno_tensor_t* srcs, const weno_tensor_t* dsts, int32_t count, const weno_params_t* p,
+                     void* d_workspace, size_t ws_bytes, void* hip_stream, weno_batch_plan_t* plan)
 {
     if (!srcs || !dsts || !plan || count < 1 || !d_workspace) return WENO_EINVAL;
     int rc = wz_check_params(p);
@@ -701,6 +713,13 @@ extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_te
     return WENO_OK;
 }
 
+extern "C" int weno_zoom2x_batched_plan(const weno_tensor_t* srcs, const weno_tensor_t* dsts, int32_t count,
+                                        const weno_params_t* p, void* d_workspace, size_t ws_bytes,
+                                        void* hip_stream, weno_batch_plan_t* plan)
+{
+    return guarded([&] { return make_plan(srcs, dsts, count, p, d_workspace, ws_bytes, hip_stream, plan); });
+}
+
 extern "C" int weno_zoom2x_batched_run(const weno_batch_plan_t* plan, void* hip_stream)
 {
     if (!plan || !plan->d_workspace || plan->count < 1 || plan->total_items < 1) return WENO_EINVAL;
@@ -762,7 +781,7 @@ extern "C" int weno_zoom2x_batched_noalloc(const weno_tensor_t* srcs, const weno
 {
     if (!srcs || !dsts || count < 1) return WENO_EINVAL;
     if (count > WENO_NOALLOC_MAX_IMAGES) return WENO_ENOSPC;
-    int rc = batched_check(srcs, dsts, count, p);
+    int rc = guarded([&] { return batched_check(srcs, dsts, count, p); });
     if (rc) return rc;
     void* ws = nullptr;
     rc = noalloc_scratch(&ws);
