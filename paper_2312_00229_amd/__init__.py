@@ -156,7 +156,7 @@ def _params_at(params, beta, k_eps, h, nbw, boundary):
     """The C struct of a call's parameters and its address, valid while the struct is held."""
     if params is None:
         return _c_params_at(beta, k_eps, h, nbw, boundary)
-    p = _params(params, beta, k_eps, h, nbw, boundary)
+    p = params.c()
     return p, ctypes.addressof(p)
 
 
